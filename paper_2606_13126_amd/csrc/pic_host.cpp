@@ -118,6 +118,8 @@ struct HostPlan {
     int64_t n_parts = 0;       // split partial slots
     int64_t n_merge = 0;       // blocks of the merge launch
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
+    int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
+    int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
 };
 
 int32_t round_up(int64_t x, int64_t m) { return (int32_t)((x + m - 1) / m * m); }
@@ -128,9 +130,10 @@ int64_t dec_head_groups(const pic_config* c) {
     return (c->num_kv_heads + per_wg - 1) / per_wg;
 }
 
-// Groups, their split policy and bases.  f32 groups hold one item per
-// (query token, query head); bf16 groups hold (row tile, KV head, split) items.
-pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp) {
+// Groups, their split policy and bases.  Prefill and float32 groups hold (row tile,
+// KV head, split) items.  `split_f32` false keeps float32 keys unsplit (for a
+// workspace without room for partials).
+pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool split_f32, HostPlan& hp) {
     hp.groups.clear();
     hp.n_parts = 0;
     const int G = c->num_q_heads / c->num_kv_heads;
@@ -190,11 +193,39 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
             return std::min<int64_t>(x.split_keys, x.tok0 + 1 - x.win) > std::min<int64_t>(y.split_keys, y.tok0 + 1 - y.win);
         });
     } else if (c->dtype == PIC_F32) {
+        // Key splits when the unsplit items leave compute units idle (two workgroups of
+        // four waves or eight of one wave share a CU): chunks of about the average
+        // work per resident workgroup, at least 128 keys, below which a split's start
+        // and its partial rows cost more than the keys.
+        int64_t max_rows = 0, token_heads = 0;
         for (auto& g : hp.groups) {
-            g.n_rt = g.n_tok;
-            g.n_split = 1;
-            g.split_keys = 0;
+            max_rows = std::max<int64_t>(max_rows, (int64_t)g.n_tok * G);
+            token_heads += (int64_t)g.n_tok * c->num_q_heads;
         }
+        if (token_heads > (1 << 22))
+            return fail(PIC_EINVAL, "batch too large for one call (split it into several calls)");
+        hp.f32_waves = max_rows <= 16 ? 1 : pic::kF32Waves;
+        const int64_t tk = pic::f32_tile_keys(hp.f32_waves), tr = hp.tile_rows();
+        const int64_t target = (int64_t)pic::kTargetCUs * (hp.f32_waves == 1 ? 8 : 2);
+        int64_t base = 0, tiles_total = 0;
+        for (auto& g : hp.groups) {
+            g.n_rt = (int32_t)(((int64_t)g.n_tok * G + tr - 1) / tr);
+            base += (int64_t)g.n_rt * c->num_kv_heads;
+            // a row tile sees the window up to its own last token
+            for (int64_t rt = 0; rt < g.n_rt; ++rt)
+                tiles_total += ((int64_t)g.tok0 + (std::min((rt + 1) * tr, (int64_t)g.n_tok * G) - 1) / G - g.win + tk) / tk *
+                               c->num_kv_heads;
+        }
+        const int64_t chunk = split_f32 && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
+                                                             : (int64_t)INT32_MAX;
+        for (auto& g : hp.groups) {
+            const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + tk - 1) / tk;
+            g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
+            g.split_keys = (int32_t)((tiles + g.n_split - 1) / g.n_split * tk);
+        }
+        std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
+            return std::min(x.split_keys, x.tok0 + x.n_tok - x.win) > std::min(y.split_keys, y.tok0 + y.n_tok - y.win);
+        });
     } else {
         // Key splits, counted in 64-key tiles.  Split when the unsplit items cannot
         // fill the chip (chunks of the average work per CU), or when some item is
@@ -231,7 +262,6 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
 
 int64_t items_of(const pic_config* c, const HostPlan& hp, const pic::Group& g) {
     if (hp.dec_kernel) return (int64_t)g.n_split * dec_head_groups(c);
-    if (c->dtype == PIC_F32) return (int64_t)g.n_tok * c->num_q_heads;
     return (int64_t)g.n_rt * c->num_kv_heads * g.n_split;
 }
 
@@ -251,16 +281,17 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
                 part += n;
                 merge += (c->num_q_heads + pic::kMergeRows - 1) / pic::kMergeRows;
             }
-        } else if (c->dtype != PIC_F32 && g.n_split > 1) {
+        } else if (g.n_split > 1) {
             part += (int64_t)g.n_rt * c->num_kv_heads * g.n_split;
-            merge += (int64_t)g.n_rt * c->num_kv_heads * (pic::kTileRows / pic::kMergeRows);
+            merge += (int64_t)g.n_rt * c->num_kv_heads * (hp.tile_rows() / pic::kMergeRows);
         }
         // a launch's lanes (blocks x threads) must stay below 2^31
         if (item > (1 << 22) || merge > (1 << 23) || part > (1 << 24))
             return fail(PIC_EINVAL, "batch too large for one call (split it into several calls)");
     }
     hp.n_items = item;
-    hp.n_parts = part;
+    // counted in slots of kTileRows rows
+    hp.n_parts = (part * hp.tile_rows() + pic::kTileRows - 1) / pic::kTileRows;
     hp.n_merge = merge;
     return PIC_OK;
 }
@@ -290,10 +321,21 @@ WsLayout ws_layout(const pic_config* c, const HostPlan& hp) {
 }
 
 // The plan of a call: groups with their split policy, then their bases.
-pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp) {
-    pic_status st = make_plan(c, b, decode, hp);
+pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool split_f32 = true) {
+    pic_status st = make_plan(c, b, decode, split_f32, hp);
     if (st) return st;
     return assign_bases(c, hp);
+}
+
+// The plan of a call with ws_bytes of workspace: float32 keys stay unsplit where the
+// partials do not fit (a workspace of the size an unsplit plan needs is enough).
+pic_status build_plan_within(const pic_config* c, const pic_batch_host* b, bool decode, size_t ws_bytes, HostPlan& hp) {
+    pic_status st = build_plan(c, b, decode, hp);
+    if (st == PIC_OK && c->dtype == PIC_F32 && hp.n_parts > 0 && ws_layout(c, hp).total > ws_bytes) {
+        hp = HostPlan{};
+        st = build_plan(c, b, decode, hp, false);
+    }
+    return st;
 }
 
 // Phase step of RoPE pair i: omega_i / 2pi revolutions per position as a 64-bit
@@ -367,7 +409,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
         return fail(PIC_EINVAL, "block tables and positions must be 4-byte aligned");
 
     HostPlan hp;
-    if ((st = build_plan(c, b, decode, hp))) return st;
+    if ((st = build_plan_within(c, b, decode, ws == nullptr ? 0 : ws_bytes, hp))) return st;
     int64_t rows = 0;
     for (auto& g : hp.groups) rows += g.n_tok;
     if (rows == 0) return PIC_OK;
@@ -433,7 +475,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     }
     const bool rope_on = c->k_prerotated == 0;
     const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, p, a, stream)
-                                : pic::launch_attention(c->dtype, c->rope_style, c->head_dim, rope_on, p, a, stream);
+                                : pic::launch_attention(c->dtype, hp.f32_waves, c->rope_style, c->head_dim, rope_on, p, a, stream);
     return hip_status(e, "attention launch");
 }
 
@@ -598,7 +640,7 @@ pic_status pic_attn_decode_noalloc(const pic_config* cfg, const pic_batch_host* 
     if (st) return st;
     if ((st = check_batch(batch))) return st;
     HostPlan hp;
-    if ((st = build_plan(cfg, batch, true, hp))) return st;
+    if ((st = build_plan_within(cfg, batch, true, pic::kScratchBytes, hp))) return st;
     const size_t need = ws_layout(cfg, hp).total;
     if (need > pic::kScratchBytes)
         return fail(PIC_EWORKSPACE, "batch needs " + std::to_string(need) + " bytes of scratch; the no-allocation "
@@ -644,19 +686,11 @@ pic_status pic_plan_debug(const pic_config* cfg, const pic_batch_host* batch, in
                 }
                 continue;
             }
-            if (cfg->dtype == PIC_F32) {
-                for (int t = 0; t < g.n_tok; ++t)
-                    for (int h = 0; h < cfg->num_q_heads; ++h) {
-                        const int32_t row = t * G + h % G;
-                        emit(g.req, h / G, row, row + 1, g.win, g.tok0 + t + 1, g.tok0, -1);
-                    }
-                continue;
-            }
             for (int kvh = 0; kvh < cfg->num_kv_heads; ++kvh)
                 for (int s = 0; s < g.n_split; ++s)
                     for (int rt = 0; rt < g.n_rt; ++rt) {
-                        const int32_t rl = rt * pic::kTileRows;
-                        const int32_t rh = std::min(rl + pic::kTileRows, g.n_tok * G);
+                        const int32_t rl = rt * hp.tile_rows();
+                        const int32_t rh = std::min(rl + hp.tile_rows(), g.n_tok * G);
                         const int32_t t_last = g.tok0 + (rh - 1) / G;
                         const int32_t kl = g.win + s * g.split_keys;
                         const int32_t kh = std::min(kl + g.split_keys, t_last + 1);

@@ -43,6 +43,13 @@ constexpr int dec_kv_per_wg(int head_dim, int hkv, int group) {
     return dec_waves(head_dim, hkv, group) / dec_col_blocks(group);
 }
 
+// float32 attention: waves of a workgroup (16 query rows each) and keys per tile.
+// A call whose every (span, KV head) has at most 16 query rows (a decode with a small
+// query group) runs one-wave workgroups, so that its rows do not leave three of
+// four waves idle.
+constexpr int kF32Waves = 4;
+constexpr int f32_tile_keys(int waves) { return waves == 1 ? 16 : 32; }
+
 // One query span of one request (prefill) or one request's last token (decode).
 // Its work items are (row tile, KV head, key split) triples -- (key split, head
 // group) for the decode kernel -- enumerated from item_base.  Partial results of
@@ -57,7 +64,7 @@ struct Group {
     int32_t q_row0;      // row of tok0 in q / o
     int32_t win;         // window start of the span's tokens
     int32_t pos_off;     // offset of the request's token 0 in `positions`
-    int32_t n_rt;        // row tiles (ceil(n_tok * G / kTileRows))
+    int32_t n_rt;        // row tiles (of kTileRows rows; float32: 16 rows per wave)
     int32_t n_split;     // key splits per (row tile, KV head)
     int32_t split_keys;  // keys per split (a multiple of kTileKeys)
     int32_t item_base;   // first item (block index) of the group; a multiple of 8 (prefill)
@@ -127,9 +134,10 @@ struct Args {
     const int32_t* block_tables;
     const int32_t* positions;
     const float* rope_table;  // [rope_len][D/2] 8-byte entries (format by dtype) or null
-    float* part_o;            // [slot][kTileRows][D] split partial outputs: prefill stores
-                              // them normalised by the split's sum as bf16, decode
-                              // unnormalised as fp32
+    float* part_o;            // [slot][kTileRows][D] split partial outputs: bf16 prefill stores
+                              // them normalised by the split's sum as bf16, decode and
+                              // float32 unnormalised as fp32 (float32 slots hold 16 rows
+                              // per wave of the workgroup)
     float* part_ml;           // [slot][kTileRows][2] running max (log2 units) and sum
     float scale_log2;         // softmax scale * log2(e)
     int32_t max_blocks;
@@ -150,7 +158,7 @@ int launch_blocks_copy(int dtype, int hkv, int d, void* k_pool, void* v_pool, vo
                        const int32_t* block_ids, int n, bool to_pool, void* stream);
 int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x,
                        int n, int heads, const int32_t* positions, void* stream);
-int launch_attention(int dtype, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
+int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_plan_upload(const PlanUpload& up, void* stream);
 

@@ -10,7 +10,7 @@
 //                  rotate, then the dot products), exp2 online softmax, window mask
 //                  of Sec. 3.1.1 with whole-block skipping, optional key splits.
 //  * merge         combines key-split partial results (log-sum-exp merge).
-//  * attn_f32      fp32 VALU flash attention for the float32 path.
+//  * attn_f32      flash attention of the float32 path on the float32 matrix cores.
 //
 // Layouts: pools [num_blocks][Hkv][16][D]; q/o [rows][Hq][D]; positions int32 per
 // token, request-major.  One workgroup of the bf16 kernel owns up to 256 query rows
@@ -349,6 +349,37 @@ __device__ __forceinline__ Group group_of(const Plan& plan, int bid) {
     return plan.g[MERGE ? plan_search<&Group::merge_base>(plan, bid) : plan_search<&Group::item_base>(plan, bid)];
 }
 
+// Item li of a group: its row tile and its cluster, the (KV head, key split) pair
+// kvh * n_split + split.
+struct ItemCoords {
+    int cluster, rt, kvh, split;
+};
+__device__ __forceinline__ ItemCoords item_coords(const Group& g, int hkv, int li) {
+    ItemCoords c;
+    const int n_clusters = hkv * g.n_split;
+    if ((hkv & 7) == 0) {
+        // blocks bid, bid+8, ... run on one XCD: give them every (split, row tile) of
+        // one KV head, so that the row tiles share K/V and the splits share Q in that
+        // XCD's L2
+        const int per_kvh = g.n_split * g.n_rt;
+        const int x = li & 7, k = li >> 3;
+        const int kv = x + 8 * (k / per_kvh), r = k % per_kvh;
+        c.cluster = kv * g.n_split + r / g.n_rt;
+        c.rt = r % g.n_rt;
+    } else if ((n_clusters & 7) == 0) {
+        // the same for the row tiles of one (KV head, split)
+        const int x = li & 7, k = li >> 3;
+        c.cluster = x + 8 * (k / g.n_rt);
+        c.rt = k % g.n_rt;
+    } else {
+        c.cluster = li / g.n_rt;
+        c.rt = li % g.n_rt;
+    }
+    c.kvh = c.cluster / g.n_split;
+    c.split = c.cluster - c.kvh * g.n_split;
+    return c;
+}
+
 // ---------------------------------------------------------------------------------
 // plan_upload: block i writes group first + i of a large batch into the table and
 // its index into the block -> group maps of the attention and merge launches.
@@ -506,29 +537,10 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     const Group g = group_of<false>(plan, bid);
     const int part_base = g.part_base;
     const int G = a.group;
-    const int n_clusters = a.hkv * g.n_split;
     const int li = bid - g.item_base;
-    if (li >= n_clusters * g.n_rt) return;
-    int cluster, rt;
-    if ((a.hkv & 7) == 0) {
-        // blocks bid, bid+8, ... run on one XCD: give them every (split, row tile) of
-        // one KV head, so that the row tiles share K/V and the splits share Q in that
-        // XCD's L2
-        const int per_kvh = g.n_split * g.n_rt;
-        const int x = li & 7, k = li >> 3;
-        const int kv = x + 8 * (k / per_kvh), r = k % per_kvh;
-        cluster = kv * g.n_split + r / g.n_rt;
-        rt = r % g.n_rt;
-    } else if ((n_clusters & 7) == 0) {
-        // the same for the row tiles of one (KV head, split)
-        const int x = li & 7, k = li >> 3;
-        cluster = x + 8 * (k / g.n_rt);
-        rt = k % g.n_rt;
-    } else {
-        cluster = li / g.n_rt;
-        rt = li % g.n_rt;
-    }
-    const int kvh = cluster / g.n_split, split = cluster - kvh * g.n_split;
+    if (li >= a.hkv * g.n_split * g.n_rt) return;
+    const ItemCoords ic = item_coords(g, a.hkv, li);
+    const int cluster = ic.cluster, rt = ic.rt, kvh = ic.kvh, split = ic.split;
     const int rows_total = g.n_tok * G;
     const int row_lo = rt * kTileRows;
     const int row_hi = min(row_lo + kTileRows, rows_total);
@@ -1562,104 +1574,382 @@ __global__ void __launch_bounds__(kMergeRows * D / 4) decode_merge(const Plan pl
 }
 
 // ---------------------------------------------------------------------------------
-// attn_f32: one wave per (query token, query head); lane holds D/64 elements.
+// attn_f32
+//
+// Flash attention of float32 tensors on the float32 matrix cores.  Workgroup = NW
+// waves (kF32Waves, or one for a call whose query rows fit one wave) x 16 query rows
+// (token x query head of one KV head's group) over one key range; wave w owns rows
+// 16 w .. 16 w + 15 as the columns of its 16x16x4 products.  A tile is TK keys, its K
+// rotated once by the thread that stages it (through registers, the next tile's loads
+// in flight under the current tile's products), 16-byte chunks XOR-swizzled by key.
+//   S^T (16 keys x 16 queries) = K Q^T     A: lane l holds K[key l%16][16 c + 4 (l/16) + e]
+//   O^T (16 dims x 16 queries) += V^T P^T  B: register r of S^T, i.e. keys 4 (l/16) + r,
+//                                          so probabilities never leave their lanes
+// Row i of output block db is dimension 64 (db / 4) + 4 i + db % 4, so that one 16-byte
+// read of a V row serves four blocks and the output leaves in 16-byte stores.
+// Bound by the matrix cores: 8 D flops per (row, key) at 64 flops per cycle and SIMD;
+// one wave per (token, head) with a shuffle sum per key took 638 us on 573 queries of
+// 8 heads over up to 1,400 keys (1 TFLOP/s), this form takes 24 us (26 TFLOP/s).
 // ---------------------------------------------------------------------------------
-template <int D, int STYLE, bool ROPE, bool TABLE>
-__global__ void __launch_bounds__(64) attn_f32(const Plan plan, const Args a) {
-    constexpr int E = D / 64;
+typedef float f32x4v_t __attribute__((ext_vector_type(4)));
+
+template <int D, int STYLE, bool ROPE, bool TABLE, int NW>
+__global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Args a) {
+    constexpr int TK = f32_tile_keys(NW);
     constexpr int HALF = D / 2;
-    const int lane = threadIdx.x;
+    constexpr int KC = D / 16;            // 16-dim contraction steps of 4 products each
+    constexpr int DB = D / 16;            // 16-dim blocks of O^T
+    constexpr int CH = D / 4;             // 16-byte chunks per row
+    constexpr int KB = TK / 16;           // 16-key blocks per tile
+    constexpr int TPK = NW * 64 / TK;     // staging threads per key
+    constexpr int KU = D / 8 / TPK;       // staged K units (two chunks, four pairs) per thread
+    constexpr int VU = CH / TPK;          // staged V chunks per thread
+    static_assert(KU >= 1 && VU >= 1 && TPK * KU * 8 == D, "staging shape");
+
+    __shared__ f32x4v_t ks[TK * CH];
+    __shared__ f32x4v_t vs[TK * CH];
+    __shared__ int vbad;                  // tile (1-based) whose V holds an infinity or NaN
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c16 = lane & 15, q4 = lane >> 4;
     const int bid = blockIdx.x;
     const Group g = group_of<false>(plan, bid);
+    const int G = a.group;
     const int li = bid - g.item_base;
-    if (li >= g.n_tok * a.hq) return;
-    const int toff = li / a.hq, h = li - toff * a.hq;
-    const int kvh = h / a.group;
-    const int t = g.tok0 + toff;
+    if (li >= a.hkv * g.n_split * g.n_rt) return;
+    const ItemCoords ic = item_coords(g, a.hkv, li);
+    const int row_lo = ic.rt * NW * 16;
+    const int row_hi = min(row_lo + NW * 16, g.n_tok * G);
+    const int t_last = g.tok0 + (row_hi - 1) / G;
+    const int kv_lo = g.win + ic.split * g.split_keys;
+    const int kv_hi = g.n_split > 1 ? min(kv_lo + g.split_keys, t_last + 1) : t_last + 1;
+    if (kv_lo >= kv_hi) return;
+    if (tid == 0) vbad = 0;
 
-    // element e of this lane is dimension d = lane + 64 e; its pair partner and
-    // frequency follow the pairing style
-    auto partner_val = [&](const float* v, int e) -> float {
-        if (STYLE == kNeox) {
-            if (E == 2) return v[1 - e];
-            return __shfl_xor(v[e], 32);
+    const int wave_row0 = row_lo + wave * 16;
+    const bool wave_live = wave_row0 < row_hi;
+    const int wave_tmin = g.tok0 + min(wave_row0, row_hi - 1) / G;
+    const int row = wave_row0 + c16;
+    const bool row_valid = row < row_hi;
+    const int toff = row_valid ? row / G : 0;
+    const int qh = ic.kvh * G + (row_valid ? row - toff * G : 0);
+    const int hi_key = min(kv_hi - 1, row_valid ? g.tok0 + toff : t_last);   // last key this lane's row may see
+
+    // cos/sin of pairs i .. i+3 at position pos
+    auto cs4 = [&](int32_t pos, int i, float* c, float* s) {
+        if (TABLE && (uint32_t)pos < (uint32_t)a.rope_len) {
+            const f32x4v_t* t = reinterpret_cast<const f32x4v_t*>(reinterpret_cast<const float2*>(a.rope_table) + (size_t)pos * HALF + i);
+            const f32x4v_t t0 = t[0], t1 = t[1];
+            c[0] = t0[0]; s[0] = t0[1]; c[1] = t0[2]; s[1] = t0[3];
+            c[2] = t1[0]; s[2] = t1[1]; c[3] = t1[2]; s[3] = t1[3];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) rope_cs(pos, a.fstep[i + e], c[e], s[e]);
         }
-        return __shfl_xor(v[e], 1);
     };
-    auto rotate = [&](float* v, int32_t pos) {
-        float pv[E];
+    // element offset in a q / K row of kernel-layout dimension d (a multiple of 4)
+    auto model_off = [&](int d) { return model_chunk(a.chunk_map, d >> 3) * 8 + (d & 7); };
+
+    // ---- queries: B operand, rotated, scaled by softmax_scale * log2(e)
+    f32x4v_t q[KC];
+    {
+        const float* qp = static_cast<const float*>(a.q) + ((size_t)(g.q_row0 + toff) * a.hq + qh) * D;
 #pragma unroll
-        for (int e = 0; e < E; ++e) pv[e] = partner_val(v, e);
+        for (int c = 0; c < KC; ++c) {
+            q[c] = *reinterpret_cast<const f32x4v_t*>(qp + model_off(16 * c + 4 * q4));
+            if (!row_valid) q[c] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+        }
+        if (ROPE) {
+            const int32_t pos = a.positions[g.pos_off + g.tok0 + toff];
+            if (STYLE == kNeox) {
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const int d = lane + 64 * e;
-            const int i = STYLE == kNeox ? (d % HALF) : d / 2;
-            const bool first = STYLE == kNeox ? d < HALF : (d & 1) == 0;
-            float c, s;
-            if (TABLE && (uint32_t)pos < (uint32_t)a.rope_len) {
-                const float2 cs = reinterpret_cast<const float2*>(a.rope_table)[(size_t)pos * HALF + i];
-                c = cs.x; s = cs.y;
+                for (int c = 0; c < KC / 2; ++c) {
+                    float cc[4], ss[4];
+                    cs4(pos, 16 * c + 4 * q4, cc, ss);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float x = q[c][e], y = q[c + KC / 2][e];
+                        q[c][e] = x * cc[e] - y * ss[e];
+                        q[c + KC / 2][e] = y * cc[e] + x * ss[e];
+                    }
+                }
             } else {
-                rope_cs(pos, a.fstep[i], c, s);
+                // pairs 8 c + 2 q4 and the next: half of the four entries that start at an even quad
+#pragma unroll
+                for (int c = 0; c < KC; ++c) {
+                    float cc[4], ss[4];
+                    cs4(pos, (8 * c + 2 * q4) & ~3, cc, ss);
+                    const int o = (q4 & 1) * 2;
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const float ce = o ? cc[2 + m] : cc[m], se = o ? ss[2 + m] : ss[m];
+                        const float x = q[c][2 * m], y = q[c][2 * m + 1];
+                        q[c][2 * m] = x * ce - y * se;
+                        q[c][2 * m + 1] = y * ce + x * se;
+                    }
+                }
             }
-            v[e] = first ? v[e] * c - pv[e] * s : v[e] * c + pv[e] * s;
         }
-    };
-
-    const float* qp = static_cast<const float*>(a.q) + ((size_t)(g.q_row0 + toff) * a.hq + h) * D;
-    // element e of this lane holds kernel-layout dimension lane + 64 e of q and K
-    int me[E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-        const int d = lane + 64 * e;
-        me[e] = model_chunk(a.chunk_map, d >> 3) * 8 + (d & 7);
+        for (int c = 0; c < KC; ++c) q[c] *= a.scale_log2;
     }
-    float q[E], o[E];
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        q[e] = qp[me[e]];
-        o[e] = 0.f;
-    }
-    if (ROPE) rotate(q, a.positions[g.pos_off + t]);
-#pragma unroll
-    for (int e = 0; e < E; ++e) q[e] *= a.scale_log2;
 
+    // ---- staging: thread tid stages part `sub` of key `sk` of every tile
     const int32_t* btab = a.block_tables + (size_t)g.req * a.max_blocks;
     const float* kpool = static_cast<const float*>(a.k_pool);
     const float* vpool = static_cast<const float*>(a.v_pool);
-    float m = kNegBig, l = 0.f;
-    for (int j = g.win; j <= t; ++j) {
-        const size_t base = (((size_t)btab[j >> 4] * a.hkv + kvh) * kBlock + (j & 15)) * D;
-        float k[E], v[E];
+    const int sk = tid / TPK, sub = tid % TPK;
+    const int n_tiles = (kv_hi - kv_lo + TK - 1) / TK;
+    int k_el[KU][2];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            k[e] = kpool[base + me[e]];
-            v[e] = vpool[base + lane + 64 * e];
-        }
-        if (ROPE) rotate(k, a.positions[g.pos_off + j]);
-        float sc = 0.f;
-#pragma unroll
-        for (int e = 0; e < E; ++e) sc += q[e] * k[e];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) sc += __shfl_xor(sc, off);
-        const float m_new = fmaxf(m, sc);
-        const float alpha = exp2f(m - m_new), p = exp2f(sc - m_new);
-        l = l * alpha + p;
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[e] = o[e] * alpha + p * v[e];
-        m = m_new;
+    for (int u = 0; u < KU; ++u) {
+        const int un = sub + u * TPK;
+        k_el[u][0] = STYLE == kNeox ? model_off(4 * un) : 8 * un;
+        k_el[u][1] = STYLE == kNeox ? model_off(HALF + 4 * un) : 8 * un + 4;
     }
-    float* op = static_cast<float*>(a.o) + ((size_t)(g.q_row0 + toff) * a.hq + h) * D;
+    int32_t m_blk = 0, m_pos = 0, m_row = 0;   // block, position and row within the block of the staged key
+    auto load_meta = [&](int t) {
+        // a key past the range stands for its last key (its score is masked)
+        const int j = min(kv_lo + t * TK + sk, kv_hi - 1);
+        m_blk = btab[j >> 4];
+        m_row = j & 15;
+        if (ROPE) m_pos = a.positions[g.pos_off + j];
+    };
+    f32x4v_t kr[KU][2], vr[VU];
+    float cr[KU][4], sr[KU][4];
+    auto load_tile = [&]() {
+        const size_t base = (((size_t)m_blk * a.hkv + ic.kvh) * kBlock + m_row) * D;
 #pragma unroll
-    for (int e = 0; e < E; ++e) op[lane + 64 * e] = o[e] / l;
+        for (int u = 0; u < KU; ++u) {
+            kr[u][0] = *reinterpret_cast<const f32x4v_t*>(kpool + base + k_el[u][0]);
+            kr[u][1] = *reinterpret_cast<const f32x4v_t*>(kpool + base + k_el[u][1]);
+        }
+#pragma unroll
+        for (int u = 0; u < VU; ++u) vr[u] = *reinterpret_cast<const f32x4v_t*>(vpool + base + 4 * (sub + u * TPK));
+        if (ROPE)
+#pragma unroll
+            for (int u = 0; u < KU; ++u) cs4(m_pos, 4 * (sub + u * TPK), cr[u], sr[u]);
+    };
+    auto store_tile = [&](int t) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) {
+            const int un = sub + u * TPK;
+            f32x4v_t x = kr[u][0], y = kr[u][1];
+            if (ROPE) {
+                if (STYLE == kNeox) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float xe = x[e], ye = y[e];
+                        x[e] = xe * cr[u][e] - ye * sr[u][e];
+                        y[e] = ye * cr[u][e] + xe * sr[u][e];
+                    }
+                } else {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const float x0 = x[2 * m], x1 = x[2 * m + 1], y0 = y[2 * m], y1 = y[2 * m + 1];
+                        x[2 * m] = x0 * cr[u][m] - x1 * sr[u][m];
+                        x[2 * m + 1] = x1 * cr[u][m] + x0 * sr[u][m];
+                        y[2 * m] = y0 * cr[u][2 + m] - y1 * sr[u][2 + m];
+                        y[2 * m + 1] = y1 * cr[u][2 + m] + y0 * sr[u][2 + m];
+                    }
+                }
+            }
+            const int ca = STYLE == kNeox ? un : 2 * un, cb = STYLE == kNeox ? un + D / 8 : 2 * un + 1;
+            ks[sk * CH + (ca ^ (sk & 15))] = x;
+            ks[sk * CH + (cb ^ (sk & 15))] = y;
+        }
+        float z = 0.f;   // NaN if some staged V element is not finite
+#pragma unroll
+        for (int u = 0; u < VU; ++u) {
+            vs[sk * CH + sub + u * TPK] = vr[u];
+            z += (vr[u][0] * 0.f + vr[u][1] * 0.f) + (vr[u][2] * 0.f + vr[u][3] * 0.f);
+        }
+        if (__builtin_amdgcn_ballot_w64(z != z) != 0 && lane == 0) vbad = t + 1;
+    };
+
+    f32x4v_t acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[db] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+    float m_run = kNegBig, l_run = 0.f;
+
+    load_meta(0);
+    load_tile();
+    if (1 < n_tiles) load_meta(1);
+    __syncthreads();   // vbad is cleared before the first tile may set it
+    for (int t = 0; t < n_tiles; ++t) {
+        store_tile(t);
+        __syncthreads();
+        if (t + 1 < n_tiles) {
+            load_tile();
+            if (t + 2 < n_tiles) load_meta(t + 2);
+        }
+        const int kt = kv_lo + t * TK;
+        if (wave_live && kt <= g.tok0 + (min(wave_row0 + 15, row_hi - 1)) / G) {
+            f32x4v_t s[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) s[kb] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < KC; ++c) {
+                f32x4v_t k[KB];
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb) k[kb] = ks[(16 * kb + c16) * CH + ((4 * c + q4) ^ c16)];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+                        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[kb][e], q[c][e], s[kb], 0, 0, 0);
+            }
+            const bool masked = kt + TK > kv_hi || kt + TK - 1 > wave_tmin;
+            if (masked) {
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (kt + 16 * kb + 4 * q4 + r > hi_key) s[kb][r] = -INFINITY;
+            }
+            float mx = kNegBig;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                mx = fmaxf(mx, fmaxf(fmaxf(s[kb][0], s[kb][1]), fmaxf(s[kb][2], s[kb][3])));
+            mx = max_xor32(max_xor16(mx));
+            const float m_new = fmaxf(m_run, mx);
+            if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < DB; ++db) acc[db] *= alpha;
+                m_run = m_new;
+            }
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    s[kb][r] = __builtin_amdgcn_exp2f(s[kb][r] - m_run);
+                    l_run += s[kb][r];
+                }
+            if (masked && vbad == t + 1) {
+                // an infinity or NaN in V must not reach rows that do not see its key
+                // (0 x Inf in the products below): one key at a time, seen rows only
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll 1
+                        for (int kq = 0; kq < 4; ++kq) {
+                            const int key = 16 * kb + 4 * kq + r;
+                            const float p = __shfl(s[kb][r], 16 * kq + c16);
+                            if (kt + key <= hi_key) {
+#pragma unroll
+                                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i)
+                                        acc[db][i] += p * vs[key * CH + 16 * (db / 4) + 4 * q4 + i][db % 4];
+                            }
+                        }
+            } else {
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int key = 16 * kb + 4 * q4 + r;
+#pragma unroll
+                        for (int h = 0; h < DB / 4; ++h) {
+                            const f32x4v_t v = vs[key * CH + 16 * h + c16];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                acc[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[e], s[kb][r], acc[4 * h + e], 0, 0, 0);
+                        }
+                    }
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- epilogue: lane l holds query column l%16 and, in element i of block db,
+    // dimension 64 (db / 4) + 16 (l/16) + 4 i + db % 4
+    const float lt = sum_xor32(sum_xor16(l_run));
+    if (!row_valid) return;
+    float* dst;
+    float inv = 1.f;
+    if (g.n_split > 1) {
+        const size_t prow = ((size_t)g.part_base + (size_t)ic.cluster * g.n_rt + ic.rt) * (NW * 16) + wave * 16 + c16;
+        dst = a.part_o + prow * D;
+        if (q4 == 0) *reinterpret_cast<float2*>(a.part_ml + prow * 2) = make_float2(m_run, lt);
+    } else {
+        dst = static_cast<float*>(a.o) + ((size_t)(g.q_row0 + toff) * a.hq + qh) * D;
+        inv = 1.f / lt;
+    }
+#pragma unroll
+    for (int h = 0; h < DB / 4; ++h)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f32x4v_t w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = acc[4 * h + e][i] * inv;
+            *reinterpret_cast<f32x4v_t*>(dst + 64 * h + 16 * q4 + 4 * i) = w;
+        }
+}
+
+// Split merge of the float32 path: the partials are unnormalised, one block per
+// kMergeRows rows of a (row tile, KV head), one 16-byte chunk of a row per thread.
+template <int D, int NW>
+__global__ void __launch_bounds__(kMergeRows * D / 4) merge_f32(const Plan plan, const Args a) {
+    constexpr int TPR = D / 4, ROWS = NW * 16, CHUNKS = ROWS / kMergeRows, U = 8;
+    const Group g = group_of<true>(plan, blockIdx.x);
+    if (g.n_split <= 1) return;
+    int li = blockIdx.x - g.merge_base;
+    if (li >= a.hkv * g.n_rt * CHUNKS) return;
+    const int r = (li % CHUNKS) * kMergeRows + (int)threadIdx.x / TPR, c4 = (int)threadIdx.x % TPR;
+    li /= CHUNKS;
+    const int kvh = li / g.n_rt, rt = li - kvh * g.n_rt, G = a.group;
+    const int row = rt * ROWS + r, row_hi = min((rt + 1) * ROWS, g.n_tok * G);
+    if (row >= row_hi) return;
+    const int n_live = min(g.n_split, (g.tok0 + (row_hi - 1) / G - g.win) / g.split_keys + 1);   // non-empty splits
+    const size_t slot0 = (size_t)g.part_base + (size_t)kvh * g.n_split * g.n_rt + rt;
+    float M = kNegBig, den = 0.f;
+    f32x4v_t num = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < n_live; s0 += U) {
+        float2 ml[U];
+        f32x4v_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const size_t prow = (slot0 + (size_t)min(s0 + u, n_live - 1) * g.n_rt) * ROWS + r;
+            ml[u] = *reinterpret_cast<const float2*>(a.part_ml + prow * 2);
+            v[u] = *reinterpret_cast<const f32x4v_t*>(a.part_o + prow * D + c4 * 4);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= n_live || ml[u].y == 0.f) continue;   // past the end, or no key of this row
+            const float m_new = fmaxf(M, ml[u].x);
+            const float c_old = __builtin_amdgcn_exp2f(M - m_new), c_new = __builtin_amdgcn_exp2f(ml[u].x - m_new);
+            num = num * c_old + c_new * v[u];
+            den = den * c_old + c_new * ml[u].y;
+            M = m_new;
+        }
+    }
+    const int toff = row / G;
+    *reinterpret_cast<f32x4v_t*>(static_cast<float*>(a.o) +
+                                 ((size_t)(g.q_row0 + toff) * a.hq + (size_t)kvh * G + (row - toff * G)) * D + c4 * 4) =
+        num * (1.f / den);
+}
+
+template <int D, int STYLE, bool ROPE, bool TABLE, int NW>
+hipError_t launch_f32_t(const Plan& plan, const Args& a, hipStream_t st) {
+    hipLaunchKernelGGL((attn_f32<D, STYLE, ROPE, TABLE, NW>), dim3(plan.n_items), dim3(NW * 64), 0, st, plan, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (plan.n_merge > 0) {
+        hipLaunchKernelGGL((merge_f32<D, NW>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 template <int D, int STYLE, bool ROPE, bool TABLE>
-hipError_t launch_attn_t(int dtype, const Plan& plan, const Args& a, hipStream_t st) {
-    if (dtype == 1) {
-        hipLaunchKernelGGL((attn_f32<D, STYLE, ROPE, TABLE>), dim3(plan.n_items), dim3(64), 0, st, plan, a);
-        return hipGetLastError();
-    }
+hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args& a, hipStream_t st) {
+    if (dtype == 1)
+        return f32_waves == 1 ? launch_f32_t<D, STYLE, ROPE, TABLE, 1>(plan, a, st)
+                              : launch_f32_t<D, STYLE, ROPE, TABLE, kF32Waves>(plan, a, st);
     hipLaunchKernelGGL((prefill_bf16<D, STYLE, ROPE, TABLE>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1698,11 +1988,11 @@ hipError_t launch_dec_d(bool rope, const Plan& plan, const Args& a, hipStream_t 
 }
 
 template <int D, int STYLE>
-hipError_t launch_attn_d(int dtype, bool rope, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_attn_d(int dtype, int f32_waves, bool rope, const Plan& plan, const Args& a, hipStream_t st) {
     const bool table = a.rope_table != nullptr && a.rope_len > 0;
-    if (!rope) return launch_attn_t<D, STYLE, false, false>(dtype, plan, a, st);
-    return table ? launch_attn_t<D, STYLE, true, true>(dtype, plan, a, st)
-                 : launch_attn_t<D, STYLE, true, false>(dtype, plan, a, st);
+    if (!rope) return launch_attn_t<D, STYLE, false, false>(dtype, f32_waves, plan, a, st);
+    return table ? launch_attn_t<D, STYLE, true, true>(dtype, f32_waves, plan, a, st)
+                 : launch_attn_t<D, STYLE, true, false>(dtype, f32_waves, plan, a, st);
 }
 
 }  // namespace
@@ -1806,14 +2096,14 @@ int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& arg
     return style == kNeox ? launch_dec_d<128, 0>(rope, plan, args, st) : launch_dec_d<128, 1>(rope, plan, args, st);
 }
 
-int launch_attention(int dtype, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
+int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
     if (plan.n_items == 0) return hipSuccess;
     hipStream_t st = (hipStream_t)stream;
     if (d == 64)
-        return style == kNeox ? launch_attn_d<64, 0>(dtype, rope, plan, args, st)
-                              : launch_attn_d<64, 1>(dtype, rope, plan, args, st);
-    return style == kNeox ? launch_attn_d<128, 0>(dtype, rope, plan, args, st)
-                          : launch_attn_d<128, 1>(dtype, rope, plan, args, st);
+        return style == kNeox ? launch_attn_d<64, 0>(dtype, f32_waves, rope, plan, args, st)
+                              : launch_attn_d<64, 1>(dtype, f32_waves, rope, plan, args, st);
+    return style == kNeox ? launch_attn_d<128, 0>(dtype, f32_waves, rope, plan, args, st)
+                          : launch_attn_d<128, 1>(dtype, f32_waves, rope, plan, args, st);
 }
 
 }  // namespace pic
