@@ -44,7 +44,7 @@ typedef int32_t pic_status;
 #define PIC_EINVAL 1       /* malformed argument (null pointer, bad shape, bad span list) */
 #define PIC_EUNSUPPORTED 2 /* well formed but not implemented (e.g. head_dim 96) */
 #define PIC_EHIP 3         /* a HIP runtime call or launch failed */
-#define PIC_EWORKSPACE 4   /* workspace smaller than pic_workspace_size() asked for */
+#define PIC_EWORKSPACE 4   /* workspace smaller than the call needs */
 
 /* element types (cfg->dtype) */
 #define PIC_BF16 0
@@ -183,8 +183,11 @@ pic_status pic_blocks_scatter(const pic_config* cfg, void* k_pool, void* v_pool,
 /* Workspace bytes that pic_attn_prefill (is_decode = 0) or pic_attn_decode
  * (is_decode = 1) needs for this configuration and batch: split-KV partial results
  * and, for batches of more than 64 groups (query spans; requests for decode), the
- * work-group table that the call writes there before its attention launch.  May be
- * 0.  Returned through *bytes (the status reports argument errors). */
+ * work-group table that the call writes there before its attention launch; for a
+ * prefill whose keys are shared by many query rows also room for a rotated copy of
+ * those keys (at most 256 MiB).  The copy, and the partial results of float32 calls,
+ * are optional: a workspace without room for them is accepted, and the call is slower.
+ * May be 0.  Returned through *bytes (the status reports argument errors). */
 pic_status pic_workspace_size(const pic_config* cfg, const pic_batch_host* batch, int32_t is_decode,
                               size_t* bytes);
 

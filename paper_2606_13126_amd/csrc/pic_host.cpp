@@ -25,6 +25,7 @@ namespace {
 
 // both structures travel as kernel arguments
 static_assert(sizeof(pic::Plan) + sizeof(pic::Args) <= 4096, "kernel arguments must stay within 4 KB");
+static_assert(sizeof(pic::KeyPlan) + sizeof(pic::Args) <= 4096, "kernel arguments must stay within 4 KB");
 static_assert(sizeof(pic::PlanUpload) <= 4096, "kernel arguments must stay within 4 KB");
 
 thread_local std::string g_error;
@@ -119,6 +120,7 @@ struct HostPlan {
     int64_t n_merge = 0;       // blocks of the merge launch
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
+    pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
 };
 
@@ -185,7 +187,6 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
         const int64_t chunk = std::max<int64_t>(4, (tiles_total + target - 1) / target);
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
-            g.n_rt = 1;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
             g.split_keys = (int32_t)(((tiles + g.n_split - 1) / g.n_split) * pic::kDecTileKeys);
         }
@@ -209,10 +210,10 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
         const int64_t target = (int64_t)pic::kTargetCUs * (hp.f32_waves == 1 ? 8 : 2);
         int64_t base = 0, tiles_total = 0;
         for (auto& g : hp.groups) {
-            g.n_rt = (int32_t)(((int64_t)g.n_tok * G + tr - 1) / tr);
-            base += (int64_t)g.n_rt * c->num_kv_heads;
+            const int32_t n_rt = pic::row_tiles(g, G, tr);
+            base += (int64_t)n_rt * c->num_kv_heads;
             // a row tile sees the window up to its own last token
-            for (int64_t rt = 0; rt < g.n_rt; ++rt)
+            for (int64_t rt = 0; rt < n_rt; ++rt)
                 tiles_total += ((int64_t)g.tok0 + (std::min((rt + 1) * tr, (int64_t)g.n_tok * G) - 1) / G - g.win + tk) / tk *
                                c->num_kv_heads;
         }
@@ -233,10 +234,10 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
         // alone at the end (chunks of a third of that average).
         int64_t base = 0, tiles_total = 0, max_item = 0;
         for (auto& g : hp.groups) {
-            g.n_rt = (int32_t)(((int64_t)g.n_tok * G + pic::kTileRows - 1) / pic::kTileRows);
+            const int32_t n_rt = pic::row_tiles(g, G, pic::kTileRows);
             const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + pic::kTileKeys - 1) / pic::kTileKeys;
-            base += (int64_t)g.n_rt * c->num_kv_heads;
-            tiles_total += (int64_t)g.n_rt * c->num_kv_heads * tiles;
+            base += (int64_t)n_rt * c->num_kv_heads;
+            tiles_total += (int64_t)n_rt * c->num_kv_heads * tiles;
             max_item = std::max(max_item, tiles);
         }
         const double avg = (double)tiles_total / pic::kTargetCUs;
@@ -262,7 +263,7 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
 
 int64_t items_of(const pic_config* c, const HostPlan& hp, const pic::Group& g) {
     if (hp.dec_kernel) return (int64_t)g.n_split * dec_head_groups(c);
-    return (int64_t)g.n_rt * c->num_kv_heads * g.n_split;
+    return (int64_t)pic::row_tiles(g, c->num_q_heads / c->num_kv_heads, hp.tile_rows()) * c->num_kv_heads * g.n_split;
 }
 
 // Assign every group its item, partial-slot and merge-block bases (one attention
@@ -282,8 +283,9 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
                 merge += (c->num_q_heads + pic::kMergeRows - 1) / pic::kMergeRows;
             }
         } else if (g.n_split > 1) {
-            part += (int64_t)g.n_rt * c->num_kv_heads * g.n_split;
-            merge += (int64_t)g.n_rt * c->num_kv_heads * (hp.tile_rows() / pic::kMergeRows);
+            const int64_t n_rt = pic::row_tiles(g, c->num_q_heads / c->num_kv_heads, hp.tile_rows());
+            part += n_rt * c->num_kv_heads * g.n_split;
+            merge += n_rt * c->num_kv_heads * (hp.tile_rows() / pic::kMergeRows);
         }
         // a launch's lanes (blocks x threads) must stay below 2^31
         if (item > (1 << 22) || merge > (1 << 23) || part > (1 << 24))
@@ -296,34 +298,97 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
     return PIC_OK;
 }
 
+size_t key_copy_bytes(const pic_config* c, int64_t blocks) {
+    return (size_t)blocks * c->num_kv_heads * pic::kBlock * c->head_dim * 2;
+}
+
 constexpr size_t kWsAlign = 256;
 size_t align_up(size_t x) { return (x + kWsAlign - 1) / kWsAlign * kWsAlign; }
 
 // Workspace layout: split partial outputs [n_parts][kTileRows][D] (sized for fp32),
 // their (max, sum) pairs [n_parts][kTileRows][2], and -- for batches of more than
 // kMaxGroups groups -- the group table with the block -> group maps.
+// The rotated key copy comes last and is optional: a workspace that ends before it is
+// accepted, and the keys are then rotated in the attention kernel.
 struct WsLayout {
-    size_t ml = 0, table = 0, item_map = 0, merge_map = 0, total = 0;
+    size_t ml = 0, table = 0, item_map = 0, merge_map = 0, need = 0, keys = 0, total = 0;
 };
 
 WsLayout ws_layout(const pic_config* c, const HostPlan& hp) {
     WsLayout w;
     const size_t parts = (size_t)hp.n_parts * pic::kTileRows;
     w.ml = parts * c->head_dim * sizeof(float);
-    w.total = w.ml + parts * 2 * sizeof(float);
+    w.need = w.ml + parts * 2 * sizeof(float);
     if (hp.groups.size() > (size_t)pic::kMaxGroups) {
-        w.table = align_up(w.total);
+        w.table = align_up(w.need);
         w.item_map = align_up(w.table + hp.groups.size() * sizeof(pic::Group));
         w.merge_map = align_up(w.item_map + (size_t)hp.n_items * sizeof(int32_t));
-        w.total = w.merge_map + (size_t)hp.n_merge * sizeof(int32_t);
+        w.need = w.merge_map + (size_t)hp.n_merge * sizeof(int32_t);
+    }
+    w.total = w.need;
+    if (hp.keys.n > 0) {
+        w.keys = align_up(w.need);
+        w.total = w.keys + key_copy_bytes(c, hp.keys.n_blocks);
     }
     return w;
+}
+
+// Whether the call rotates its keys once, into the workspace, and the segments to
+// rotate.  Rotating in the attention kernel costs every row tile about 0.043 ns per key
+// and KV head (64 keys x 256 rows take 2.5 us instead of 1.8 us on one of 256 CUs);
+// the copy costs about 0.07 ns per key and KV head (512 bytes moved, part of them in the
+// Infinity Cache) and a launch between two others, about 10 us.  kv_write + attention,
+// rotating in the attention kernel against copy + attention: one 33,280-token prompt
+// (20 row tiles per key) 903 against 784 us; 16 tails of 128 tokens over 4,096 keys (2
+// per key) 161 against 167 us; a 256-query tail over 5,376 keys (4 per key) 41 against
+// 50 us.
+void plan_keys(const pic_config* c, HostPlan& hp) {
+    hp.keys.n = 0;
+    if (c->dtype != PIC_BF16 || c->k_prerotated || hp.dec_kernel) return;
+    const int G = c->num_q_heads / c->num_kv_heads;
+    struct Run {
+        int32_t req, lo, hi, pos_off;
+    };
+    std::vector<Run> runs;
+    double staged = 0.0;   // keys times the row tiles that see them
+    for (const auto& g : hp.groups) {
+        runs.push_back(Run{g.req, g.win, g.tok0 + g.n_tok, g.pos_off});
+        for (int rt = 0; rt < pic::row_tiles(g, G, pic::kTileRows); ++rt)
+            staged += (double)(g.tok0 + (std::min((int64_t)(rt + 1) * pic::kTileRows, (int64_t)g.n_tok * G) - 1) / G + 1 - g.win);
+    }
+    std::sort(runs.begin(), runs.end(), [](const Run& x, const Run& y) { return x.req != y.req ? x.req < y.req : x.lo < y.lo; });
+    // runs of a request that overlap or touch make one segment
+    std::vector<Run> segs;
+    for (const Run& r : runs) {
+        if (!segs.empty() && segs.back().req == r.req && r.lo <= segs.back().hi) segs.back().hi = std::max(segs.back().hi, r.hi);
+        else segs.push_back(r);
+    }
+    int64_t keys = 0, blocks = 0;
+    for (const Run& r : segs) {
+        keys += r.hi - r.lo;
+        blocks += ((r.hi - 1) >> 4) - (r.lo >> 4) + 1;
+    }
+    const double gain_us = c->num_kv_heads * (0.043e-3 * staged - 0.07e-3 * (double)keys) - 10.0;
+    if (gain_us <= 0 || segs.size() > (size_t)pic::kMaxGroups || key_copy_bytes(c, blocks) > pic::kMaxKeyCopy) return;
+    hp.keys.n = (int32_t)segs.size();
+    int32_t blk = 0;
+    for (size_t i = 0; i < segs.size(); ++i) {
+        hp.keys.seg[i] = pic::KeySegment{segs[i].req, segs[i].lo, segs[i].hi, segs[i].pos_off, blk};
+        blk += ((segs[i].hi - 1) >> 4) - (segs[i].lo >> 4) + 1;
+    }
+    hp.keys.n_blocks = blk;
+    for (auto& g : hp.groups)
+        for (int i = 0; i < hp.keys.n; ++i) {
+            const pic::KeySegment& sg = hp.keys.seg[i];
+            if (sg.req == g.req && sg.lo <= g.win && g.win < sg.hi) g.krot0 = sg.blk0 - (sg.lo >> 4);
+        }
 }
 
 // The plan of a call: groups with their split policy, then their bases.
 pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool split_f32 = true) {
     pic_status st = make_plan(c, b, decode, split_f32, hp);
     if (st) return st;
+    plan_keys(c, hp);
     return assign_bases(c, hp);
 }
 
@@ -415,8 +480,8 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     if (rows == 0) return PIC_OK;
     if (!q || !o) return fail(PIC_EINVAL, "q and o must not be NULL");
     const WsLayout wl = ws_layout(c, hp);
-    if (wl.total > 0 && (ws == nullptr || ws_bytes < wl.total))
-        return fail(PIC_EWORKSPACE, "workspace needs " + std::to_string(wl.total) + " bytes");
+    if (wl.need > 0 && (ws == nullptr || ws_bytes < wl.need))
+        return fail(PIC_EWORKSPACE, "workspace needs " + std::to_string(wl.need) + " bytes");
 
     pic::Args a{};
     phase_steps(c, a.fstep);
@@ -432,6 +497,8 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     a.rope_len = table ? rope->len : 0;
     char* wsb = static_cast<char*>(ws);
     a.part_o = hp.n_parts ? reinterpret_cast<float*>(wsb) : nullptr;
+    const bool copy_keys = hp.keys.n > 0 && ws != nullptr && ws_bytes >= wl.total;
+    a.k_rot = copy_keys ? wsb + wl.keys : nullptr;
     a.part_ml = hp.n_parts ? reinterpret_cast<float*>(wsb + wl.ml) : nullptr;
     const double scale = c->softmax_scale > 0.f ? (double)c->softmax_scale : 1.0 / std::sqrt((double)c->head_dim);
     a.scale_log2 = (float)(scale * 1.4426950408889634);
@@ -473,6 +540,9 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
             if ((st = hip_status(pic::launch_plan_upload(u, stream), "plan upload launch"))) return st;
         }
     }
+    if (copy_keys &&
+        (st = hip_status(pic::launch_rope_keys(c->rope_style, c->head_dim, hp.keys, a, stream), "key rotation launch")))
+        return st;
     const bool rope_on = c->k_prerotated == 0;
     const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, p, a, stream)
                                 : pic::launch_attention(c->dtype, hp.f32_waves, c->rope_style, c->head_dim, rope_on, p, a, stream);
@@ -641,7 +711,7 @@ pic_status pic_attn_decode_noalloc(const pic_config* cfg, const pic_batch_host* 
     if ((st = check_batch(batch))) return st;
     HostPlan hp;
     if ((st = build_plan_within(cfg, batch, true, pic::kScratchBytes, hp))) return st;
-    const size_t need = ws_layout(cfg, hp).total;
+    const size_t need = ws_layout(cfg, hp).need;
     if (need > pic::kScratchBytes)
         return fail(PIC_EWORKSPACE, "batch needs " + std::to_string(need) + " bytes of scratch; the no-allocation "
                     "entry point has " + std::to_string(pic::kScratchBytes) + " (use pic_attn_decode with a workspace)");
@@ -686,9 +756,10 @@ pic_status pic_plan_debug(const pic_config* cfg, const pic_batch_host* batch, in
                 }
                 continue;
             }
+            const int32_t n_rt = pic::row_tiles(g, G, hp.tile_rows());
             for (int kvh = 0; kvh < cfg->num_kv_heads; ++kvh)
                 for (int s = 0; s < g.n_split; ++s)
-                    for (int rt = 0; rt < g.n_rt; ++rt) {
+                    for (int rt = 0; rt < n_rt; ++rt) {
                         const int32_t rl = rt * hp.tile_rows();
                         const int32_t rh = std::min(rl + hp.tile_rows(), g.n_tok * G);
                         const int32_t t_last = g.tok0 + (rh - 1) / G;
@@ -696,7 +767,7 @@ pic_status pic_plan_debug(const pic_config* cfg, const pic_batch_host* batch, in
                         const int32_t kh = std::min(kl + g.split_keys, t_last + 1);
                         if (kl >= kh) continue;
                         const int32_t slot =
-                            g.n_split > 1 ? g.part_base + (kvh * g.n_split + s) * g.n_rt + rt : -1;
+                            g.n_split > 1 ? g.part_base + (kvh * g.n_split + s) * n_rt + rt : -1;
                         emit(g.req, kvh, rl, rh, kl, kh, g.tok0, slot);
                     }
         }

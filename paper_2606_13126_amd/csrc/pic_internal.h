@@ -2,6 +2,7 @@
 // (pic_kernels.hip).  Not part of the public ABI.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -64,13 +65,20 @@ struct Group {
     int32_t q_row0;      // row of tok0 in q / o
     int32_t win;         // window start of the span's tokens
     int32_t pos_off;     // offset of the request's token 0 in `positions`
-    int32_t n_rt;        // row tiles (of kTileRows rows; float32: 16 rows per wave)
     int32_t n_split;     // key splits per (row tile, KV head)
     int32_t split_keys;  // keys per split (a multiple of kTileKeys)
     int32_t item_base;   // first item (block index) of the group; a multiple of 8 (prefill)
     int32_t part_base;   // first partial slot (split groups)
     int32_t merge_base;  // first block of the merge launch (split groups)
+    int32_t krot0;       // block of the call's rotated key copy that holds sequence block 0 (may be negative)
 };
+
+// Row tiles of a group whose workgroups hold tile_rows query rows (kTileRows; float32:
+// 16 per wave).  Not a field: a dispatch whose arguments pass about 3.8 KB takes 2 us
+// longer on the host (44.6 against 47.0 us for a one-request decode step).
+__host__ __device__ inline int32_t row_tiles(const Group& g, int32_t group, int32_t tile_rows) {
+    return (int32_t)(((int64_t)g.n_tok * group + tile_rows - 1) / tile_rows);
+}
 
 // The work of one call: one attention launch of n_items blocks and one merge launch
 // of n_merge blocks, whatever the number of groups.  Up to kMaxGroups groups travel
@@ -88,6 +96,21 @@ struct Plan {
     const int32_t* merge_map; // device [n_merge]: group of each merge block
     Group g[kMaxGroups];
 };
+
+// A prefill whose keys are each seen by many row tiles rotates them once, into a copy
+// in the workspace: one segment per run of keys of a request that some query sees.
+struct KeySegment {
+    int32_t req;
+    int32_t lo, hi;      // keys [lo, hi)
+    int32_t pos_off;     // offset of the request's token 0 in `positions`
+    int32_t blk0;        // block of the copy that holds block lo / kBlock of the sequence
+};
+struct KeyPlan {
+    int32_t n;
+    int32_t n_blocks;    // blocks of the copy
+    KeySegment seg[kMaxGroups];
+};
+constexpr size_t kMaxKeyCopy = (size_t)256 << 20;   // bytes of the copy: what the Infinity Cache holds
 
 // Arguments of one plan-upload launch: groups [first, first + n) of the call, and
 // where the block ranges of the chunk's last group end.
@@ -131,6 +154,7 @@ struct Args {
     void* o;
     const void* k_pool;
     const void* v_pool;
+    const void* k_rot;        // the call's rotated copy of the keys its queries see, in the pool's layout, or null
     const int32_t* block_tables;
     const int32_t* positions;
     const float* rope_table;  // [rope_len][D/2] 8-byte entries (format by dtype) or null
@@ -160,6 +184,7 @@ int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeStep
                        int n, int heads, const int32_t* positions, void* stream);
 int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
+int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, void* stream);
 int launch_plan_upload(const PlanUpload& up, void* stream);
 
 // Device scratch of the no-allocation entry point: kScratchBytes on each device,

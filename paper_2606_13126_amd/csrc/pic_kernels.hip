@@ -9,6 +9,7 @@
 //                  (Sec. 3.2.2: load tile, look up cos/sin at the tile's positions,
 //                  rotate, then the dot products), exp2 online softmax, window mask
 //                  of Sec. 3.1.1 with whole-block skipping, optional key splits.
+//  * rope_keys     the call's rotated copy of its keys, where many row tiles share them.
 //  * merge         combines key-split partial results (log-sum-exp merge).
 //  * attn_f32      flash attention of the float32 path on the float32 matrix cores.
 //
@@ -37,6 +38,12 @@ constexpr float kNegBig = -1.0e30f;  // finite "minus infinity" for running maxi
 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// Round two floats to bf16 (round to nearest even) and pack them, lo first.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+    bf16x2_t v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
 
 // (a.lo * b.lo + a.hi * b.hi) of two bf16 pairs, fp32 result.
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b) {
@@ -123,6 +130,35 @@ __device__ __forceinline__ Words4 rot4_gptj(uint32_t w0, uint32_t w1, uint32_t w
     return Words4{{w0, w1, w2, w3}};
 }
 
+// Two rotate-half pairs (elements 2m and 2m+1 of both halves) in plain float32
+// arithmetic, for a kernel that is bound by memory and leaves the schedule to the
+// compiler.  (A dot product occupies the matrix pipe: 64 of them beside 16 MFMAs of
+// another wave of the SIMD take 375 ns, either alone 138 and 248, where 64 FMAs add
+// nothing.  The attention kernels still rotate by dot products: 8 FMA-form vector
+// instructions more per pair cost prefill_bf16 2% on 16 tails over 4,096 keys.)
+__device__ __forceinline__ void rot2_fma(uint32_t& A, uint32_t& B, uint32_t e0, uint32_t e1) {
+    const float x0 = bf_lo(A), x1 = bf_hi(A), y0 = bf_lo(B), y1 = bf_hi(B);
+    const float c0 = bf_lo(e0), s0 = bf_hi(e0), c1 = bf_lo(e1), s1 = bf_hi(e1);
+    A = pack_bf16(__builtin_fmaf(x0, c0, -(y0 * s0)), __builtin_fmaf(x1, c1, -(y1 * s1)));
+    B = pack_bf16(__builtin_fmaf(y0, c0, x0 * s0), __builtin_fmaf(y1, c1, x1 * s1));
+}
+
+// One key's share of 2 PW pairs: NeoX x and y runs, GPT-J the pairs in order.
+template <int STYLE, int PW>
+__device__ __forceinline__ void rotate_runs(uint32_t (&k)[2][PW], const uint32_t* cs) {
+    if (STYLE == kNeox) {
+#pragma unroll
+        for (int i = 0; i < PW; ++i) rot2_fma(k[0][i], k[1][i], cs[2 * i], cs[2 * i + 1]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2 * PW; ++i) {
+            uint32_t& w = k[i / PW][i % PW];
+            const float x = bf_lo(w), y = bf_hi(w), c = bf_lo(cs[i]), sn = bf_hi(cs[i]);
+            w = pack_bf16(__builtin_fmaf(x, c, -(y * sn)), __builtin_fmaf(y, c, x * sn));
+        }
+    }
+}
+
 // (a.lo, b.lo) and (a.hi, b.hi) of two bf16 pairs: the rotate-half pairing brings
 // element i of one 8-dim run together with element i of the run half a head
 // further; one byte permute each (bytes 0-3 of the selector pick from a, 4-7 from b)
@@ -134,12 +170,6 @@ __device__ __forceinline__ uint32_t pair_hi(uint32_t a, uint32_t b) { return __b
 __device__ __forceinline__ float sum2_bf16(uint32_t a, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, 0x3f803f80u), c,
                                            false);
-}
-
-// Round two floats to bf16 (round to nearest even) and pack them, lo first.
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
-    bf16x2_t v = {(__bf16)lo, (__bf16)hi};
-    return __builtin_bit_cast(uint32_t, v);
 }
 
 // ---------------------------------------------------------------------------------
@@ -354,26 +384,26 @@ __device__ __forceinline__ Group group_of(const Plan& plan, int bid) {
 struct ItemCoords {
     int cluster, rt, kvh, split;
 };
-__device__ __forceinline__ ItemCoords item_coords(const Group& g, int hkv, int li) {
+__device__ __forceinline__ ItemCoords item_coords(const Group& g, int hkv, int n_rt, int li) {
     ItemCoords c;
     const int n_clusters = hkv * g.n_split;
     if ((hkv & 7) == 0) {
         // blocks bid, bid+8, ... run on one XCD: give them every (split, row tile) of
         // one KV head, so that the row tiles share K/V and the splits share Q in that
         // XCD's L2
-        const int per_kvh = g.n_split * g.n_rt;
+        const int per_kvh = g.n_split * n_rt;
         const int x = li & 7, k = li >> 3;
         const int kv = x + 8 * (k / per_kvh), r = k % per_kvh;
-        c.cluster = kv * g.n_split + r / g.n_rt;
-        c.rt = r % g.n_rt;
+        c.cluster = kv * g.n_split + r / n_rt;
+        c.rt = r % n_rt;
     } else if ((n_clusters & 7) == 0) {
         // the same for the row tiles of one (KV head, split)
         const int x = li & 7, k = li >> 3;
-        c.cluster = x + 8 * (k / g.n_rt);
-        c.rt = k % g.n_rt;
+        c.cluster = x + 8 * (k / n_rt);
+        c.rt = k % n_rt;
     } else {
-        c.cluster = li / g.n_rt;
-        c.rt = li % g.n_rt;
+        c.cluster = li / n_rt;
+        c.rt = li % n_rt;
     }
     c.kvh = c.cluster / g.n_split;
     c.split = c.cluster - c.kvh * g.n_split;
@@ -395,6 +425,11 @@ __global__ void __launch_bounds__(256) plan_upload_kernel(const PlanUpload u) {
     for (int b = g.item_base + (int)threadIdx.x; b < item_end; b += blockDim.x) u.item_map[b] = gi;
     for (int b = g.merge_base + (int)threadIdx.x; b < merge_end; b += blockDim.x) u.merge_map[b] = gi;
 }
+
+template <int I>
+struct Idx {
+    static constexpr int value = I;
+};
 
 constexpr int kWaves = kTileRows / 32;   // wave w owns rows [32w, 32w+32); 2 waves per SIMD
 constexpr int kThreads = kWaves * 64;
@@ -437,6 +472,10 @@ typedef __attribute__((address_space(3))) const uint16_t lds_u16_t;
 // an LDS array element as an LDS-space pointer (constant offsets then fold into
 // the instruction's offset field)
 __device__ __forceinline__ lds_u16_t* as_lds(const uint16_t* p) { return (lds_u16_t*)p; }
+
+typedef __attribute__((address_space(3))) const bf16x8_t lds_bf16x8_t;
+// the LDS byte address of a shared array
+__device__ __forceinline__ uint32_t lds_addr(const uint16_t* p) { return (uint32_t)(uintptr_t)(lds_u16_t*)p; }
 
 // Transposing LDS read: within each 16-lane group, lane i receives element i%4 of
 // the 8-byte rows that lanes i/4, i/4+4, i/4+8, i/4+12 point at.
@@ -481,6 +520,10 @@ __device__ __forceinline__ uint32_t lds_offset(const void* p) {
 __device__ __forceinline__ void dma_lds16(const void* src, const void* lds_wave_base) {
     asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(lds_offset(lds_wave_base)) : "memory");
 }
+// the same from a wave-uniform address plus a 32-bit byte offset per lane
+__device__ __forceinline__ void dma_lds16_s(const void* base, uint32_t off, const void* lds_wave_base) {
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds_offset(lds_wave_base)) : "memory");
+}
 __device__ __forceinline__ void dma_lds4(const void* src, const void* lds_wave_base) {
     asm volatile("s_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(src), "{m0}"(lds_offset(lds_wave_base)) : "memory");
 }
@@ -495,6 +538,84 @@ __device__ __forceinline__ void barrier_keep_vmem() {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+
+// ---------------------------------------------------------------------------------
+// rope_keys: the call's rotated copy of the keys its queries see, in the pool's layout
+// with blocks in sequence order (and a row's 8-element chunks in kernel order).  One
+// workgroup per cache block: 8 lanes per key (D / 16 pairs each), every second KV head.
+// Bound by memory: each key read and written once (33,280 keys of
+// 8 KV heads, 136 MB, in 24-28 us: 5 TB/s).
+// ---------------------------------------------------------------------------------
+template <int D, int STYLE, bool TABLE>
+__global__ void __launch_bounds__(256) rope_keys(const KeyPlan plan, const Args a) {
+    constexpr int HALF = D / 2, P = D / 16, PW = P / 2, U = 4;
+    typedef uint32_t run_t __attribute__((ext_vector_type(PW)));
+    int lo = 0, up = plan.n - 1;
+    while (lo < up) {
+        const int mid = (lo + up + 1) >> 1;
+        if (plan.seg[mid].blk0 <= (int)blockIdx.x) lo = mid;
+        else up = mid - 1;
+    }
+    const KeySegment sg = plan.seg[lo];
+    const int kb = (sg.lo >> 4) + (int)blockIdx.x - sg.blk0;       // sequence block
+    const int key = ((int)threadIdx.x >> 3) & 15, sc = (int)threadIdx.x & 7;
+    const int j = kb * kBlock + key;
+    if (j < sg.lo || j >= sg.hi) return;                           // no query sees it
+    const int blk = a.block_tables[(size_t)sg.req * a.max_blocks + kb];
+    const int32_t pos = a.positions[sg.pos_off + j];
+    int src[2], dst[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        dst[h] = key * D + (STYLE == kNeox ? h * HALF + sc * P : sc * 2 * P + h * P);
+        src[h] = key * D + model_chunk(a.chunk_map, (dst[h] % D) >> 3) * 8 + (dst[h] & 7);
+    }
+    const uint16_t* kp = static_cast<const uint16_t*>(a.k_pool) + (size_t)(uint32_t)blk * a.hkv * kBlock * D;
+    uint16_t* op = static_cast<uint16_t*>(const_cast<void*>(a.k_rot)) + (size_t)blockIdx.x * a.hkv * kBlock * D;
+    uint32_t cs[P];
+    const bool in_table = TABLE && (uint32_t)pos < (uint32_t)a.rope_len;
+    if (in_table) {
+        const uint32_t* tp = reinterpret_cast<const uint32_t*>(a.rope_table) + (size_t)pos * HALF + sc * P;
+#pragma unroll
+        for (int i = 0; i < P; ++i) cs[i] = tp[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            float c, sn;
+            rope_cs(pos, a.fstep[sc * P + i], c, sn);
+            cs[i] = bf16_entry(c, sn);
+        }
+    }
+    // KV heads hp, hp + 2, ..: the loads of four go out together
+    for (int h0 = (int)threadIdx.x >> 7; h0 < a.hkv; h0 += 2 * U) {
+        run_t x[U], y[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint16_t* row = kp + (size_t)min(h0 + 2 * u, a.hkv - 1) * kBlock * D;
+            x[u] = *reinterpret_cast<const run_t*>(row + src[0]);
+            y[u] = *reinterpret_cast<const run_t*>(row + src[1]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (h0 + 2 * u >= a.hkv) break;
+            uint32_t k[2][PW];
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                k[0][i] = x[u][i];
+                k[1][i] = y[u][i];
+            }
+            rotate_runs<STYLE, PW>(k, cs);
+            run_t ox, oy;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                ox[i] = k[0][i];
+                oy[i] = k[1][i];
+            }
+            uint16_t* row = op + (size_t)(h0 + 2 * u) * kBlock * D;
+            *reinterpret_cast<run_t*>(row + dst[0]) = ox;
+            *reinterpret_cast<run_t*>(row + dst[1]) = oy;
+        }
+    }
+}
 
 // ---------------------------------------------------------------------------------
 // prefill_bf16
@@ -513,7 +634,7 @@ __device__ __forceinline__ void barrier_keep_vmem() {
 //   for 16-key steps; the matching A operand (32 dims x the same 8 keys per lane)
 //   comes straight from the untransposed V tile through ds_read_b64_tr_b16.
 // ---------------------------------------------------------------------------------
-template <int D, int STYLE, bool ROPE, bool TABLE>
+template <int D, int STYLE, bool TABLE>
 __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const Plan plan, const Args a) {
     constexpr int KD = D / 16;    // 16-wide contraction steps of QK^T
     constexpr int DB = D / 32;    // 32-row blocks of O^T
@@ -537,9 +658,9 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     const Group g = group_of<false>(plan, bid);
     const int part_base = g.part_base;
     const int G = a.group;
-    const int li = bid - g.item_base;
-    if (li >= a.hkv * g.n_split * g.n_rt) return;
-    const ItemCoords ic = item_coords(g, a.hkv, li);
+    const int li = bid - g.item_base, n_rt = row_tiles(g, a.group, kTileRows);
+    if (li >= a.hkv * g.n_split * n_rt) return;
+    const ItemCoords ic = item_coords(g, a.hkv, n_rt, li);
     const int cluster = ic.cluster, rt = ic.rt, kvh = ic.kvh, split = ic.split;
     const int rows_total = g.n_tok * G;
     const int row_lo = rt * kTileRows;
@@ -552,7 +673,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     // phase steps of the in-kernel cos/sin: staged in LDS when every position needs
     // them (no table); with a table only positions outside it read them, from the
     // kernel arguments
-    if (ROPE && !TABLE) {
+    if (!TABLE) {
         for (int i = tid; i < HALF; i += kThreads) fstep[i] = a.fstep[i];
     }
     const uint64_t* fsteps = TABLE ? a.fstep : fstep;
@@ -575,7 +696,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
 #pragma unroll
         for (int kd = 0; kd < KD; ++kd)   // KD loads on every lane (a row past the tile reads the group's first)
             qraw[kd] = *reinterpret_cast<const u32x4_t*>(qp + model_chunk(a.chunk_map, 2 * kd + hi) * 8);
-        if (ROPE && row_valid) qpos = a.positions[g.pos_off + g.tok0 + toff];
+        if (row_valid) qpos = a.positions[g.pos_off + g.tok0 + toff];
     };
     auto q_finish = [&]() {   // rotate, scale by softmax_scale*log2(e), round to bf16
         float xf[KD][8];
@@ -587,7 +708,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
                 xf[kd][2 * m] = bf_lo(w);
                 xf[kd][2 * m + 1] = bf_hi(w);
             }
-        if (ROPE) {
+        {
             const int32_t pos = qpos;
             if (STYLE == kNeox) {
 #pragma unroll
@@ -640,14 +761,14 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     const uint16_t* kpool = static_cast<const uint16_t*>(a.k_pool);
     const uint16_t* vpool = static_cast<const uint16_t*>(a.v_pool);
 
-    // staging role of this thread (K through registers when it is rotated): keys
+    // staging role of this thread (K, through registers): keys
     // kk + u * (kThreads / TPK), u < SU, of every tile, 16-element slice sc
-    const bool stager = ROPE && tid < NSTAGE;
+    const bool stager = tid < NSTAGE;
     const int kk = tid / TPK, sc = tid - (tid / TPK) * TPK;
     constexpr int KSTEP = kThreads / TPK;
     const int kt0 = kv_lo & ~(kBlock - 1);
     const int n_tiles = (kv_hi - kt0 + BN - 1) / BN;
-    // direct global->LDS role (V always, K too without RoPE): lane `lane` of wave
+    // direct global->LDS role (V): lane `lane` of wave
     // `wave` fills 16-byte chunk p = (DPW*wave + i)*64 + lane of the tile, i.e. row
     // p / CH, physical chunk p % CH, which holds logical chunk (p % CH) ^ swz(row)
     constexpr int DPW = BN * CH / (64 * kWaves);
@@ -670,7 +791,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     auto dma_meta = [&](int t) {
         if (t >= n_tiles) return;
         const int kt = kt0 + t * BN;
-        if (ROPE && wave_u == 0) {
+        if (wave_u == 0) {
             dma_lds4(a.positions + g.pos_off + clamp_key(kt, kt + lane), &mpos[t & 1][0]);
         } else if (wave_u == 1 && lane < BN / kBlock) {
             const int blk = min((kt >> 4) + lane, (kv_hi - 1) >> 4);
@@ -706,7 +827,6 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
         for (int i = 0; i < DPW; ++i) {
             const int lds_off = (DPW * wave_u + i) * 64 * 8;
             dma_lds16(vpool + row_off[i], &vs[buf][lds_off]);
-            if (!ROPE) dma_lds16(kpool + row_off[i], &ks[buf][lds_off]);
         }
     };
     auto load_meta = [&](int t, TileRegs* rr) {
@@ -1001,7 +1121,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
             *reinterpret_cast<u32x2_t*>(stage + l32 * D + ((c ^ (l32 & (CH - 1))) << 3) + 4 * hi) = w;
         }
     __builtin_amdgcn_wave_barrier();
-    const size_t slot = (size_t)part_base + (size_t)cluster * g.n_rt + rt;
+    const size_t slot = (size_t)part_base + (size_t)cluster * n_rt + rt;
     constexpr int RPI = 64 / CH;   // rows per store instruction
 #pragma unroll
     for (int i = 0; i < 32 / RPI; ++i) {
@@ -1024,6 +1144,415 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
 }
 
 // ---------------------------------------------------------------------------------
+// prefill_direct
+//
+// The prefill over keys that need no rotation on their way: a pool of rotated keys
+// (k_prerotated), or the call's own rotated copy (RK, rope_keys).  Rows, tiles, operand
+// layouts and arithmetic are those of prefill_bf16; K and V both go straight to LDS.
+//
+// A wave alternates a product phase (scores of tile t, then P V of tile t - 1: matrix
+// cores and LDS reads only) with a vector phase (copies, softmax of tile t), a barrier
+// after each.  Waves 4-7 run one phase behind waves 0-3, so each SIMD always has one
+// wave in either phase.  Four slots of K and of V (128 KB at D = 128) keep the copies
+// three phases ahead.
+//
+// Bound by power: with random operands the chip holds 16 of these products and their
+// LDS reads on every SIMD at 0.65 us where zero operands take 0.45, so 64 keys x 256
+// rows cannot take less than 1.3 us; 1.65-1.8 us here (a tail of 512 x 64 queries over
+// 33,280 rotated keys: 432-460 us, 477-505 us with both waves of a SIMD in step).
+// ---------------------------------------------------------------------------------
+template <int D, int STYLE, bool ROPE, bool TABLE, bool RK>
+__global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_direct(const Plan plan, const Args a) {
+    constexpr int KD = D / 16;    // 16-wide contraction steps of QK^T
+    constexpr int DB = D / 32;    // 32-row blocks of O^T
+    constexpr int CH = D / 8;     // 16-byte chunks per row
+    constexpr int HALF = D / 2;
+    constexpr int BN = 64;
+    constexpr int NH = BN / 32;   // 32-key halves per tile
+    constexpr int DPW = BN * CH / (64 * kWaves);   // copies per wave and tile, each of K and V
+    constexpr int RPC = 64 / CH;  // rows per copy
+    static_assert(kWaves == 8 && BN == kTileKeys, "a wave copies 8 rows of one cache block per tile");
+
+    constexpr int NS = 4;         // slots of each ring
+    __shared__ __attribute__((aligned(1024))) uint16_t ks[NS][BN * D];
+    __shared__ __attribute__((aligned(1024))) uint16_t vs[NS][BN * D];
+    __shared__ uint64_t fstep[HALF];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int bid = blockIdx.x;
+    const Group g = group_of<false>(plan, bid);
+    const int G = a.group;
+    const int li = bid - g.item_base, n_rt = row_tiles(g, a.group, kTileRows);
+    if (li >= a.hkv * g.n_split * n_rt) return;
+    const ItemCoords ic = item_coords(g, a.hkv, n_rt, li);
+    const int kvh = ic.kvh;
+    const int row_lo = ic.rt * kTileRows;
+    const int row_hi = min(row_lo + kTileRows, g.n_tok * G);
+    const int t_last = g.tok0 + (row_hi - 1) / G;
+    const int kv_lo = g.win + ic.split * g.split_keys;
+    const int kv_hi = min(kv_lo + g.split_keys, t_last + 1);
+    if (kv_lo >= kv_hi) return;
+
+    if (ROPE && !TABLE) {
+        for (int i = tid; i < HALF; i += kThreads) fstep[i] = a.fstep[i];
+    }
+    const uint64_t* fsteps = TABLE ? a.fstep : fstep;
+
+    const int wave_row0 = row_lo + wave * 32;
+    const bool wave_live = wave_row0 < row_hi;
+    const int wave_tmin = g.tok0 + min(wave_row0, row_hi - 1) / G;
+    const int row = wave_row0 + l32;
+    const bool row_valid = row < row_hi;
+    const int toff = row_valid ? row / G : 0;
+    const int hl = row_valid ? row - toff * G : 0;
+    const int row_tok = row_valid ? g.tok0 + toff : t_last;
+    const int hi_key = min(kv_hi - 1, row_tok);   // last key this lane's row may see
+
+    // ---- the queries' loads and positions first, then the first tiles' loads
+    bf16x8_t qb[KD];
+    u32x4_t qraw[KD];
+    int32_t qpos = 0;
+    {
+        const uint16_t* qp = static_cast<const uint16_t*>(a.q) +
+                             ((size_t)(g.q_row0 + toff) * a.hq + (size_t)kvh * G + hl) * D;
+        if (ROPE && row_valid) qpos = a.positions[g.pos_off + g.tok0 + toff];
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd) qraw[kd] = *reinterpret_cast<const u32x4_t*>(qp + model_chunk(a.chunk_map, 2 * kd + hi) * 8);
+    }
+
+    const int32_t* btab = a.block_tables + (size_t)g.req * a.max_blocks;
+    const int kt0 = kv_lo & ~(kBlock - 1);
+    const int n_tiles = (kv_hi - kt0 + BN - 1) / BN;
+    // Wave w brings in rows 8 w .. 8 w + 7 of every tile: half of one cache block, so one
+    // block id per tile and wave.  Lane i of copy c fills 16-byte chunk (DPW w + c) 64 + i
+    // of the tile, which holds logical chunk (i % CH) ^ swz(row).
+    const int last_blk = (kv_hi - 1) >> 4;
+    const int wrow = 8 * (wave & 1) + lane / CH;          // row within the block (copy 0)
+    uint32_t lane_off[DPW];                               // byte offset within a block of one head
+#pragma unroll
+    for (int c = 0; c < DPW; ++c) lane_off[c] = (uint32_t)(((wrow + c * RPC) * D + (((lane % CH) ^ swz<D>(wrow + c * RPC)) << 3)) * 2);
+    const size_t blk_bytes = (size_t)a.hkv * kBlock * D * 2;
+    const char* khead = static_cast<const char*>(RK ? a.k_rot : a.k_pool) + (size_t)kvh * kBlock * D * 2;
+    const char* vhead = static_cast<const char*>(a.v_pool) + (size_t)kvh * kBlock * D * 2;
+    // block id of this wave's rows in tile t, through the scalar unit; looked up one step
+    // before its use, so that nothing waits for it
+    auto nid = [&](int t) { return scalar_load(btab, min((kt0 >> 4) + 4 * t + (wave >> 1), last_blk)); };
+    // first visible key of a tile that the window cuts stands for the keys outside it
+    auto copy_rows = [&](const char* head, int t, int blk, int blk_cut, uint16_t* lds) {
+        const int kt = kt0 + t * BN;
+        uint16_t* dst = lds + wave * DPW * 64 * 8;
+        if (kt >= kv_lo && kt + BN <= kv_hi) {
+            const char* src = head + (size_t)(uint32_t)blk * blk_bytes;
+#pragma unroll
+            for (int c = 0; c < DPW; ++c) dma_lds16_s(src, lane_off[c], dst + c * 64 * 8);
+        } else {
+            const int cut = max(kt, kv_lo);
+#pragma unroll
+            for (int c = 0; c < DPW; ++c) {
+                const int r = wrow + c * RPC, j = kt + 16 * (wave >> 1) + r;
+                const bool in = j >= kv_lo && j < kv_hi;
+                const uint32_t off = (uint32_t)((in ? r : cut & 15) * D + (((lane % CH) ^ swz<D>(r)) << 3)) * 2;
+                dma_lds16(head + (size_t)(uint32_t)(in ? blk : blk_cut) * blk_bytes + off, dst + c * 64 * 8);
+            }
+        }
+    };
+    // block of the tile's first visible key (where the window cuts the tile)
+    auto cut_id = [&](int t) {
+        const int kt = kt0 + t * BN;
+        return kt >= kv_lo && kt + BN <= kv_hi ? 0 : scalar_load(btab, max(kt, kv_lo) >> 4);
+    };
+
+    // Copies of tile t's V and tile t + 1's K go out together, the two that the same
+    // product phase reads.
+    int id0 = 0, id1 = 0, id2 = 0;   // block ids of tiles t, t + 1 and t + 2
+    auto issue = [&](int t) {
+        id0 = id1;
+        id1 = id2;
+        if (t + 1 < n_tiles) {
+            const int kb = g.krot0 + (kt0 >> 4) + 4 * (t + 1);   // the tile's first block in the rotated copy
+            if (RK) copy_rows(khead, t + 1, kb + (wave >> 1), max(kb, g.krot0 + (kv_lo >> 4)), ks[(t + 1) % NS]);
+            else copy_rows(khead, t + 1, id1, cut_id(t + 1), ks[(t + 1) % NS]);
+        }
+        id2 = nid(t + 2);
+        if (t >= 0 && t < n_tiles) copy_rows(vhead, t, id0, cut_id(t), vs[t % NS]);
+    };
+    id2 = nid(0);
+    issue(-1);
+    issue(0);
+    issue(1);
+    if (ROPE && !TABLE) __syncthreads();   // phase steps in LDS
+
+    // ---- queries: rotate, scale by softmax_scale * log2(e), round to bf16
+    {
+        float xf[KD][8];
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const uint32_t w = row_valid ? qraw[kd][m] : 0u;
+                xf[kd][2 * m] = bf_lo(w);
+                xf[kd][2 * m + 1] = bf_hi(w);
+            }
+        if (ROPE) {
+            if (STYLE == kNeox) {
+#pragma unroll
+                for (int kd = 0; kd < KD / 2; ++kd) {
+                    float c[8], s[8];
+                    rope_cs_n<8, TABLE>(a.rope_table, a.rope_len, HALF, fsteps, qpos, kd * 16 + 8 * hi, c, s);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float x = xf[kd][e], y = xf[kd + KD / 2][e];
+                        xf[kd][e] = x * c[e] - y * s[e];
+                        xf[kd + KD / 2][e] = y * c[e] + x * s[e];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int kd = 0; kd < KD; ++kd) {
+                    float c[4], s[4];
+                    rope_cs_n<4, TABLE>(a.rope_table, a.rope_len, HALF, fsteps, qpos, kd * 8 + 4 * hi, c, s);
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const float x = xf[kd][2 * m], y = xf[kd][2 * m + 1];
+                        xf[kd][2 * m] = x * c[m] - y * s[m];
+                        xf[kd][2 * m + 1] = y * c[m] + x * s[m];
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int kd = 0; kd < KD; ++kd) {
+            u32x4_t w;
+#pragma unroll
+            for (int m = 0; m < 4; ++m)
+                w[m] = pack_bf16(xf[kd][2 * m] * a.scale_log2, xf[kd][2 * m + 1] * a.scale_log2);
+            qb[kd] = __builtin_bit_cast(bf16x8_t, w);
+        }
+    }
+
+    f32x16_t acc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) acc[db] = f32x16_t{};
+    float m_run = kNegBig, l_run = 0.f;
+    // The S^T chain starts from nbias = -m_run (0 while m_run is kNegBig, i.e. no
+    // visible key yet), so that it returns the scores relative to the reference
+    // maximum and the exponentials need no subtraction; `thr` is the shifted
+    // maximum above which the reference moves (8, or any score before the first).
+    f32x16_t nbias = f32x16_t{};
+    float thr = kNegBig;
+    bf16x8_t pb[2 * NH];   // probabilities of the previous tile
+
+    // LDS byte addresses (slot 0) of the operands' first pieces.  The swizzle is an XOR,
+    // so the other contraction steps and dimension blocks are XORs of constants, made
+    // where they are used: held in registers they would cost 14 of the 256.
+    uint32_t k_addr = lds_addr(&ks[0][0]) + (uint32_t)(l32 * D + ((hi ^ swz<D>(l32)) << 3)) * 2;
+    uint32_t v_addr;
+    {
+        const int q16 = (lane >> 4) & 1, kq = (lane & 15) >> 2, dq = 4 * (lane & 3);
+        const int key = 4 * hi + kq, d = q16 * 16 + dq;
+        v_addr = lds_addr(&vs[0][0]) + (uint32_t)(key * D + (((d >> 3) ^ swz<D>(key)) << 3) + (d & 7)) * 2;
+    }
+    constexpr int kSwz8 = D == 128 ? 2 : 4;   // swz(key + 8) = swz(key) ^ kSwz8
+
+    f32x16_t s[NH];
+    // product phase: the scores of tile t (slot S) and O^T += V^T P^T of tile t - 1
+    auto products = [&](auto slot, auto scores, auto outputs) {
+        constexpr int S = decltype(slot)::value % NS;
+        constexpr bool kS = decltype(scores)::value, kO = decltype(outputs)::value;
+        if (!wave_live) return;
+        __builtin_amdgcn_s_setprio(1);
+        asm volatile("" : "+v"(k_addr), "+v"(v_addr));   // not loop constants: see their definition
+        const uint32_t kb = k_addr + S * BN * D * 2, vb = v_addr + (S + NS - 1) % NS * BN * D * 2;
+        if (kS) {
+#pragma unroll
+            for (int kd = 0; kd < KD; ++kd)
+#pragma unroll
+                for (int mb = 0; mb < NH; ++mb) {
+                    const bf16x8_t af = *(lds_bf16x8_t*)((kb ^ (kd << 5)) + mb * 32 * D * 2);
+                    s[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, qb[kd], kd == 0 ? nbias : s[mb], 0, 0, 0);
+                }
+        }
+        if (kO) {
+#pragma unroll
+            for (int k4 = 0; k4 < 2 * NH; ++k4)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const uint32_t row0 = 16 * k4 * D * 2;
+                    const s16x4_t both[2] = {
+                        lds_read_tr((lds_u16_t*)((vb ^ (db << 6)) + row0)),
+                        lds_read_tr((lds_u16_t*)((vb ^ (db << 6) ^ (kSwz8 << 4)) + 8 * D * 2 + row0))};
+                    acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, both), pb[k4], acc[db], 0, 0, 0);
+                }
+        }
+        // operand reads stay six products ahead
+        constexpr int A = 6, NK = kS ? KD * NH : 0, NV = kO ? 2 * NH * DB : 0;
+        if constexpr (kS) {
+#pragma unroll
+            for (int i = 0; i < A; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
+        } else {
+#pragma unroll
+            for (int i = 0; i < A; ++i) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < NK - A; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                              // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        if constexpr (kO) {
+#pragma unroll
+            for (int i = 0; i < NV - (kS ? 0 : A); ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < A; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    // vector phase: mask, running maximum, probabilities of tile t
+    auto softmax = [&](int t) {
+        if (!wave_live) return;
+        const int kt = kt0 + t * BN;
+        if (kt < kv_lo || kt + BN > kv_hi || kt + BN - 1 > wave_tmin) {
+#pragma unroll
+            for (int mb = 0; mb < NH; ++mb) {
+                const int base = kt + mb * 32 + 4 * hi;
+                const int lo = max(kv_lo - base, 0), top = min(hi_key - base, 31);
+                const uint32_t upto = (2u << (uint32_t)max(top, 0)) - 1u;
+                const uint32_t vis = (top < lo) ? 0u : (upto & ~((1u << (uint32_t)min(lo, 31)) - 1u));
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    const int c = 8 * (j >> 2) + (j & 3);
+                    s[mb][j] = (vis & (1u << c)) ? s[mb][j] : -INFINITY;
+                }
+            }
+        }
+        float mx = kNegBig;
+#pragma unroll
+        for (int mb = 0; mb < NH; ++mb)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[mb][j]);
+        mx = max_xor32(mx);
+        if (__builtin_amdgcn_ballot_w64(mx > thr) != 0) {
+            const float m_off = m_run > kNegBig ? m_run : 0.f;   // what the chain subtracted
+            const float m_new = fmaxf(m_run, mx + m_off);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db) acc[db] *= alpha;
+            m_run = m_new;
+            const bool seen = m_new > kNegBig;
+            const float d = seen ? m_new - m_off : 0.f;
+#pragma unroll
+            for (int mb = 0; mb < NH; ++mb) s[mb] -= d;
+            const float nb = seen ? -m_new : 0.f;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) nbias[j] = nb;
+            thr = seen ? 8.f : kNegBig;
+        }
+        float part[2] = {0.f, 0.f};
+#pragma unroll
+        for (int mb = 0; mb < NH; ++mb)
+#pragma unroll
+            for (int k2 = 0; k2 < 2; ++k2) {
+                u32x4_t w;
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const float p0 = __builtin_amdgcn_exp2f(s[mb][8 * k2 + 2 * m]);
+                    const float p1 = __builtin_amdgcn_exp2f(s[mb][8 * k2 + 2 * m + 1]);
+                    w[m] = pack_bf16(p0, p1);
+                    part[m & 1] = sum2_bf16(w[m], part[m & 1]);
+                }
+                // computed in this phase: left alone, the compiler moves the exponentials
+                // past the barrier, in between the products that use them
+                asm volatile("" : "+v"(w));
+                pb[2 * mb + k2] = __builtin_bit_cast(bf16x8_t, w);
+            }
+        l_run += part[0] + part[1];
+        asm volatile("" : "+v"(l_run));
+    };
+    // keys copied as they are: what the products of step t + 1 read has landed (this
+    // wave's share): only those issued after them, of issue(t + 1), may be in flight
+    auto landed = [&](int t) {
+        if (t + 2 < n_tiles) wait_vmem_n<2 * DPW>();
+        else if (t + 1 < n_tiles) wait_vmem_n<DPW>();
+        else wait_vmem();
+    };
+    const int pong = wave >> 2;   // waves 4-7 run one phase behind waves 0-3
+    if (2 < n_tiles) wait_vmem_n<4 * DPW>();   // K of tile 0
+    else wait_vmem();
+    barrier_keep_vmem();
+    if (pong) barrier_keep_vmem();
+    auto step = [&](auto slot, auto first, int t) {
+        constexpr int S = decltype(slot)::value;
+        products(slot, std::true_type{}, std::integral_constant<bool, !decltype(first)::value>{});
+        landed(t);
+        barrier_keep_vmem();
+        issue(t + 2);
+        softmax(t);
+        barrier_keep_vmem();
+    };
+    step(Idx<0>{}, std::true_type{}, 0);
+    int t = 1;
+    for (; t < n_tiles; t += 4) {
+        step(Idx<1>{}, std::false_type{}, t);
+        if (t + 1 < n_tiles) step(Idx<2>{}, std::false_type{}, t + 1);
+        if (t + 2 < n_tiles) step(Idx<3>{}, std::false_type{}, t + 2);
+        if (t + 3 < n_tiles) step(Idx<0>{}, std::false_type{}, t + 3);
+    }
+    switch (n_tiles & 3) {
+        case 0: products(Idx<0>{}, std::false_type{}, std::true_type{}); break;
+        case 1: products(Idx<1>{}, std::false_type{}, std::true_type{}); break;
+        case 2: products(Idx<2>{}, std::false_type{}, std::true_type{}); break;
+        default: products(Idx<3>{}, std::false_type{}, std::true_type{}); break;
+    }
+    if (!pong) barrier_keep_vmem();
+    __syncthreads();   // the slots become the epilogue's staging rows
+
+    // ---- epilogue: normalise (a split by its own sum, its running maximum and sum
+    // stored beside it), round to bf16 and store.  The rows pass through this wave's
+    // own 32 rows of the now idle K/V tile slots (chunks XOR-swizzled by row), so
+    // that each global store writes whole 16-byte chunks of 64 / CH complete rows.
+    const float lt = sum_xor32(l_run);
+    if (!wave_live) return;
+    const bool is_split = g.n_split > 1;
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    uint16_t* stage = (wave < kWaves / 2 ? &ks[0][0] : &vs[0][0]) + (wave % (kWaves / 2)) * 32 * D;
+    static_assert(2 * BN >= 32 * (kWaves / 2), "epilogue staging rows");
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int c = db * 4 + q4;   // dims 8c .. 8c+7 of the row; this lane holds half of them
+            const u32x2_t w = {pack_bf16(acc[db][4 * q4] * inv, acc[db][4 * q4 + 1] * inv),
+                               pack_bf16(acc[db][4 * q4 + 2] * inv, acc[db][4 * q4 + 3] * inv)};
+            *reinterpret_cast<u32x2_t*>(stage + l32 * D + ((c ^ (l32 & (CH - 1))) << 3) + 4 * hi) = w;
+        }
+    __builtin_amdgcn_wave_barrier();
+    const size_t slot = (size_t)g.part_base + (size_t)ic.cluster * n_rt + ic.rt;
+    constexpr int RPI = 64 / CH;   // rows per store instruction
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = i * RPI + lane / CH, c = lane % CH;
+        const u32x4_t v = *reinterpret_cast<const u32x4_t*>(stage + r * D + ((c ^ (r & (CH - 1))) << 3));
+        const int rr = wave_row0 + r;
+        if (rr >= row_hi) continue;
+        uint16_t* dst;
+        if (is_split) {
+            dst = reinterpret_cast<uint16_t*>(a.part_o) + (slot * kTileRows + (rr - row_lo)) * D;
+        } else {
+            const int to = rr / G, h = rr - to * G;
+            dst = static_cast<uint16_t*>(a.o) + ((size_t)(g.q_row0 + to) * a.hq + (size_t)kvh * G + h) * D;
+        }
+        *reinterpret_cast<u32x4_t*>(dst + c * 8) = v;
+    }
+    if (is_split && hi == 0 && row_valid)   // the lane's row is row_lo + 32 wave + l32
+        *reinterpret_cast<float2*>(a.part_ml + (slot * kTileRows + (32 * wave + (int)(threadIdx.x & 31))) * 2) =
+            make_float2(m_run, lt);
+}
+
+// ---------------------------------------------------------------------------------
 // merge: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s over the non-empty splits
 // of one (row tile, KV head), as a streaming log-sum-exp merge.  One block per
 // kMergeRows rows, 8 dims (16 bytes of bf16) of a row per thread; the loads of 8 splits are issued
@@ -1037,11 +1566,12 @@ __global__ void __launch_bounds__(kMergeRows * D / 8) merge_kernel(const Plan pl
     const Group g = group_of<true>(plan, blockIdx.x);
     const int part_base = g.part_base, merge_base = g.merge_base;
     if (g.n_split <= 1) return;
+    const int n_rt = row_tiles(g, a.group, kTileRows);
     int li = blockIdx.x - merge_base;
-    if (li >= a.hkv * g.n_rt * CHUNKS) return;
+    if (li >= a.hkv * n_rt * CHUNKS) return;
     const int chunk = li % CHUNKS;
     li /= CHUNKS;
-    const int kvh = li / g.n_rt, rt = li - (li / g.n_rt) * g.n_rt;
+    const int kvh = li / n_rt, rt = li - (li / n_rt) * n_rt;
     const int G = a.group;
     const int row_lo = rt * kTileRows;
     const int row_hi = min(row_lo + kTileRows, g.n_tok * G);
@@ -1052,7 +1582,7 @@ __global__ void __launch_bounds__(kMergeRows * D / 8) merge_kernel(const Plan pl
     const int r = chunk * kMergeRows + (int)threadIdx.x / TPR;
     const int q8 = (int)threadIdx.x % TPR;
     if (row_lo + r >= row_hi) return;
-    const size_t slot0 = (size_t)part_base + (size_t)kvh * g.n_split * g.n_rt + rt;
+    const size_t slot0 = (size_t)part_base + (size_t)kvh * g.n_split * n_rt + rt;
     float M = kNegBig, den = 0.f;
     float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const uint16_t* part = reinterpret_cast<const uint16_t*>(a.part_o);
@@ -1064,7 +1594,7 @@ __global__ void __launch_bounds__(kMergeRows * D / 8) merge_kernel(const Plan pl
             ml[u] = make_float2(kNegBig, 0.f);
             v[u] = u32x4_t{0, 0, 0, 0};
             if (s0 + u < n_live) {
-                const size_t slot = slot0 + (size_t)(s0 + u) * g.n_rt;
+                const size_t slot = slot0 + (size_t)(s0 + u) * n_rt;
                 ml[u] = *reinterpret_cast<const float2*>(a.part_ml + (slot * kTileRows + r) * 2);
                 v[u] = *reinterpret_cast<const u32x4_t*>(part + (slot * kTileRows + r) * D + q8 * 8);
             }
@@ -1126,11 +1656,6 @@ struct DecStage {
     uint16_t k[HW * kDecKeys * D];   // [head][key][D], chunks swizzled by key
     uint16_t v[HW * kDecKeys * D];
     uint32_t tab[ROPE ? kDecKeys * D / 2 : 4];  // [key][pair] bf16 (c, s), 16-byte chunks swizzled by key
-};
-
-template <int I>
-struct Idx {
-    static constexpr int value = I;
 };
 
 // ---------------------------------------------------------------------------------
@@ -1615,9 +2140,9 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     const int bid = blockIdx.x;
     const Group g = group_of<false>(plan, bid);
     const int G = a.group;
-    const int li = bid - g.item_base;
-    if (li >= a.hkv * g.n_split * g.n_rt) return;
-    const ItemCoords ic = item_coords(g, a.hkv, li);
+    const int li = bid - g.item_base, n_rt = row_tiles(g, a.group, NW * 16);
+    if (li >= a.hkv * g.n_split * n_rt) return;
+    const ItemCoords ic = item_coords(g, a.hkv, n_rt, li);
     const int row_lo = ic.rt * NW * 16;
     const int row_hi = min(row_lo + NW * 16, g.n_tok * G);
     const int t_last = g.tok0 + (row_hi - 1) / G;
@@ -1872,7 +2397,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     float* dst;
     float inv = 1.f;
     if (g.n_split > 1) {
-        const size_t prow = ((size_t)g.part_base + (size_t)ic.cluster * g.n_rt + ic.rt) * (NW * 16) + wave * 16 + c16;
+        const size_t prow = ((size_t)g.part_base + (size_t)ic.cluster * n_rt + ic.rt) * (NW * 16) + wave * 16 + c16;
         dst = a.part_o + prow * D;
         if (q4 == 0) *reinterpret_cast<float2*>(a.part_ml + prow * 2) = make_float2(m_run, lt);
     } else {
@@ -1897,15 +2422,16 @@ __global__ void __launch_bounds__(kMergeRows * D / 4) merge_f32(const Plan plan,
     constexpr int TPR = D / 4, ROWS = NW * 16, CHUNKS = ROWS / kMergeRows, U = 8;
     const Group g = group_of<true>(plan, blockIdx.x);
     if (g.n_split <= 1) return;
+    const int n_rt = row_tiles(g, a.group, ROWS);
     int li = blockIdx.x - g.merge_base;
-    if (li >= a.hkv * g.n_rt * CHUNKS) return;
+    if (li >= a.hkv * n_rt * CHUNKS) return;
     const int r = (li % CHUNKS) * kMergeRows + (int)threadIdx.x / TPR, c4 = (int)threadIdx.x % TPR;
     li /= CHUNKS;
-    const int kvh = li / g.n_rt, rt = li - kvh * g.n_rt, G = a.group;
+    const int kvh = li / n_rt, rt = li - kvh * n_rt, G = a.group;
     const int row = rt * ROWS + r, row_hi = min((rt + 1) * ROWS, g.n_tok * G);
     if (row >= row_hi) return;
     const int n_live = min(g.n_split, (g.tok0 + (row_hi - 1) / G - g.win) / g.split_keys + 1);   // non-empty splits
-    const size_t slot0 = (size_t)g.part_base + (size_t)kvh * g.n_split * g.n_rt + rt;
+    const size_t slot0 = (size_t)g.part_base + (size_t)kvh * g.n_split * n_rt + rt;
     float M = kNegBig, den = 0.f;
     f32x4v_t num = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < n_live; s0 += U) {
@@ -1913,7 +2439,7 @@ __global__ void __launch_bounds__(kMergeRows * D / 4) merge_f32(const Plan plan,
         f32x4v_t v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const size_t prow = (slot0 + (size_t)min(s0 + u, n_live - 1) * g.n_rt) * ROWS + r;
+            const size_t prow = (slot0 + (size_t)min(s0 + u, n_live - 1) * n_rt) * ROWS + r;
             ml[u] = *reinterpret_cast<const float2*>(a.part_ml + prow * 2);
             v[u] = *reinterpret_cast<const f32x4v_t*>(a.part_o + prow * D + c4 * 4);
         }
@@ -1950,7 +2476,14 @@ hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args&
     if (dtype == 1)
         return f32_waves == 1 ? launch_f32_t<D, STYLE, ROPE, TABLE, 1>(plan, a, st)
                               : launch_f32_t<D, STYLE, ROPE, TABLE, kF32Waves>(plan, a, st);
-    hipLaunchKernelGGL((prefill_bf16<D, STYLE, ROPE, TABLE>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+    if constexpr (ROPE) {
+        if (a.k_rot != nullptr)
+            hipLaunchKernelGGL((prefill_direct<D, STYLE, true, TABLE, true>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+        else
+            hipLaunchKernelGGL((prefill_bf16<D, STYLE, TABLE>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+    } else {
+        hipLaunchKernelGGL((prefill_direct<D, STYLE, false, false, false>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (plan.n_merge > 0) {
@@ -1978,6 +2511,15 @@ hipError_t launch_dec_t(const Plan& plan, const Args& a, hipStream_t st) {
     if (dec_waves(D, a.hkv, a.group) == 2) return launch_dec_w<D, STYLE, ROPE, TABLE, 2>(plan, a, st);
     if (dec_waves(D, a.hkv, a.group) == 4) return launch_dec_w<D, STYLE, ROPE, TABLE, 4>(plan, a, st);
     return launch_dec_w<D, STYLE, ROPE, TABLE, dec_heads(D)>(plan, a, st);
+}
+
+template <int D, int STYLE>
+hipError_t launch_rope_keys_d(const KeyPlan& plan, const Args& a, hipStream_t st) {
+    if (a.rope_table != nullptr && a.rope_len > 0)
+        hipLaunchKernelGGL((rope_keys<D, STYLE, true>), dim3(plan.n_blocks), dim3(256), 0, st, plan, a);
+    else
+        hipLaunchKernelGGL((rope_keys<D, STYLE, false>), dim3(plan.n_blocks), dim3(256), 0, st, plan, a);
+    return hipGetLastError();
 }
 
 template <int D, int STYLE>
@@ -2086,6 +2628,12 @@ int launch_plan_upload(const PlanUpload& up, void* stream) {
     if (up.n <= 0) return hipSuccess;
     hipLaunchKernelGGL(plan_upload_kernel, dim3((unsigned)up.n), dim3(256), 0, (hipStream_t)stream, up);
     return hipGetLastError();
+}
+
+int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, void* stream) {
+    hipStream_t st = (hipStream_t)stream;
+    if (d == 64) return style == kNeox ? launch_rope_keys_d<64, 0>(plan, args, st) : launch_rope_keys_d<64, 1>(plan, args, st);
+    return style == kNeox ? launch_rope_keys_d<128, 0>(plan, args, st) : launch_rope_keys_d<128, 1>(plan, args, st);
 }
 
 int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
