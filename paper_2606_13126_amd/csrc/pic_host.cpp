@@ -119,6 +119,7 @@ struct HostPlan {
     int64_t n_parts = 0;       // split partial slots
     int64_t n_merge = 0;       // blocks of the merge launch
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
+    int merge_ways = 1;        // thread rows that share a query head's splits in the decode merge (1 or kMergeRows)
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
     pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
@@ -189,6 +190,8 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
             const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
             g.split_keys = (int32_t)(((tiles + g.n_split - 1) / g.n_split) * pic::kDecTileKeys);
+            // a merge block loads up to 8 splits at once; more of them go eight ways
+            if (g.n_split > 8) hp.merge_ways = pic::kMergeRows;
         }
         std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
             return std::min<int64_t>(x.split_keys, x.tok0 + 1 - x.win) > std::min<int64_t>(y.split_keys, y.tok0 + 1 - y.win);
@@ -280,7 +283,8 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
         if (hp.dec_kernel) {
             if (g.n_split > 1) {
                 part += n;
-                merge += (c->num_q_heads + pic::kMergeRows - 1) / pic::kMergeRows;
+                const int64_t rows = pic::kMergeRows / hp.merge_ways;   // query heads per block
+                merge += (c->num_q_heads + rows - 1) / rows;
             }
         } else if (g.n_split > 1) {
             const int64_t n_rt = pic::row_tiles(g, c->num_q_heads / c->num_kv_heads, hp.tile_rows());
@@ -544,7 +548,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
         (st = hip_status(pic::launch_rope_keys(c->rope_style, c->head_dim, hp.keys, a, stream), "key rotation launch")))
         return st;
     const bool rope_on = c->k_prerotated == 0;
-    const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, p, a, stream)
+    const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, hp.merge_ways, p, a, stream)
                                 : pic::launch_attention(c->dtype, hp.f32_waves, c->rope_style, c->head_dim, rope_on, p, a, stream);
     return hip_status(e, "attention launch");
 }

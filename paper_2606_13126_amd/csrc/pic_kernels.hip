@@ -322,39 +322,75 @@ __global__ void __launch_bounds__(256) rope_table_kernel(void* __restrict__ tabl
 }
 
 // ---------------------------------------------------------------------------------
-// rope_rotate: x[row][h][:] <- R_{pos[row]} x[row][h][:], one thread per pair.
+// rope_rotate: x[row][h][:] <- R_{pos[row]} x[row][h][:], eight pairs (16 elements) per
+// thread in 16-byte accesses.  Bound by memory; one pair per thread in 2-byte accesses
+// took 12.1 us for 2,176 rows of 32 heads x 128 dims of bf16 (36 MB moved), this form
+// 6.7 us.
 // ---------------------------------------------------------------------------------
 template <typename T, int STYLE>
-__global__ void __launch_bounds__(256) rope_rotate_kernel(T* __restrict__ x, int64_t n_pairs, int heads, int d,
+__global__ void __launch_bounds__(256) rope_rotate_kernel(T* __restrict__ x, int64_t n_units, int heads, int d,
                                                           int rot_half, RopeSteps steps,
                                                           const int32_t* __restrict__ positions,
                                                           const void* __restrict__ table, int rope_len) {
+    constexpr int V = 16 / sizeof(T);              // elements per access
+    typedef T vec_t __attribute__((ext_vector_type(V)));
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_pairs) return;
-    const int half = d / 2;
-    const int64_t rh = idx / half;                 // row * heads + h
-    const int i = (int)(idx - rh * half);
-    if (i >= rot_half) return;                     // past the rotary width: unchanged
-    const int32_t pos = positions[rh / heads];
-    float c, s;
+    if (idx >= n_units) return;
+    const int upr = d / 16, half = d / 2;          // units per row of one head: 4 or 8
+    const int64_t rh = idx / upr;                  // row * heads + h
+    const int i0 = (int)(idx - rh * upr) * 8;      // first pair
+    if (i0 >= rot_half) return;                    // past the rotary width: unchanged
+    const int32_t pos = positions[rh <= UINT32_MAX ? (uint32_t)rh / (uint32_t)heads : rh / heads];
+    // NeoX: elements i0 .. i0 + 7 of both halves (rot_half is a multiple of 8); GPT-J: 2 i0 .. 2 i0 + 15
+    T* run[2] = {x + rh * d + (STYLE == kNeox ? i0 : 2 * i0), x + rh * d + (STYLE == kNeox ? i0 + rot_half : 2 * i0 + 8)};
+    T v[16];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 8; k += V) {
+            const vec_t w = *reinterpret_cast<const vec_t*>(run[h] + k);
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[8 * h + k + e] = w[e];
+        }
+    float c[8], s[8];
     if (table != nullptr && (uint32_t)pos < (uint32_t)rope_len) {
-        if (sizeof(T) == 4) {
-            const uint2 v = static_cast<const uint2*>(table)[(size_t)pos * half + i];
-            c = __uint_as_float(v.x);
-            s = __uint_as_float(v.y);
-        } else {
-            const uint32_t v = static_cast<const uint32_t*>(table)[(size_t)pos * half + i];
-            c = bf_lo(v);
-            s = bf_hi(v);
+        const u32x4_t* t = reinterpret_cast<const u32x4_t*>(static_cast<const char*>(table) +
+                                                            ((size_t)pos * half + i0) * (sizeof(T) == 4 ? 8 : 4));
+#pragma unroll
+        for (int k = 0; k < (sizeof(T) == 4 ? 4 : 2); ++k) {
+            const u32x4_t w = t[k];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (sizeof(T) == 4) {
+                    (e & 1 ? s : c)[2 * k + e / 2] = __uint_as_float(w[e]);
+                } else {
+                    c[4 * k + e] = bf_lo(w[e]);
+                    s[4 * k + e] = bf_hi(w[e]);
+                }
+            }
         }
     } else {
-        rope_cs(pos, steps.s[i], c, s);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) rope_cs(pos, steps.s[i0 + k], c[k], s[k]);
     }
-    T* row = x + rh * d;
-    const int ia = STYLE == kNeox ? i : 2 * i, ib = STYLE == kNeox ? i + rot_half : 2 * i + 1;
-    const float a = (float)row[ia], b = (float)row[ib];
-    row[ia] = (T)(a * c - b * s);
-    row[ib] = (T)(b * c + a * s);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (STYLE != kNeox && i0 + k >= rot_half) break;
+        T& ta = v[STYLE == kNeox ? k : 2 * k];
+        T& tb = v[STYLE == kNeox ? 8 + k : 2 * k + 1];
+        const float a = (float)ta, b = (float)tb;
+        ta = (T)(a * c[k] - b * s[k]);
+        tb = (T)(b * c[k] + a * s[k]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int k = 0; k < 8; k += V) {
+            vec_t w;
+#pragma unroll
+            for (int e = 0; e < V; ++e) w[e] = v[8 * h + k + e];
+            *reinterpret_cast<vec_t*>(run[h] + k) = w;
+        }
 }
 
 // A wave-uniform element read through the scalar unit (the value lands in an
@@ -2048,19 +2084,39 @@ __global__ void __launch_bounds__(HW * 64, 1) decode_bf16(const Plan plan, const
     }
 }
 
-// decode merge: one block per (request, kMergeRows query heads), one float4 of a
-// row per thread; the (max, sum) pairs and partial rows of up to 8 splits are
-// loaded together before they are combined (streaming log-sum-exp)
-template <int D, int HW>
+// One split's partial row (four dimensions per thread) into a running log-sum-exp merge.
+struct Merged {
+    float M = kNegBig, den = 0.f;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    __device__ __forceinline__ void add(float m, float l, const float4& v) {
+        const float m_new = fmaxf(M, m);
+        const float c_old = __builtin_amdgcn_exp2f(M - m_new), c_new = __builtin_amdgcn_exp2f(m - m_new);
+        num.x = num.x * c_old + c_new * v.x;
+        num.y = num.y * c_old + c_new * v.y;
+        num.z = num.z * c_old + c_new * v.z;
+        num.w = num.w * c_old + c_new * v.w;
+        den = den * c_old + c_new * l;
+        M = m_new;
+    }
+};
+
+// decode merge: one float4 of a query head's row per thread.  WAYS = 1: a block per
+// (request, kMergeRows query heads), the (max, sum) pairs and partial rows of up to 8
+// splits loaded together before they are combined.  WAYS = 8, for more splits than
+// that: a block per query head, whose eight thread rows take every eighth split (four
+// loads in flight each) and meet in LDS.  Bound by the round trips of its loads: 25
+// splits of one request take 4.8 us in eight ways, 10.5 us one after another.
+template <int D, int HW, int WAYS>
 __global__ void __launch_bounds__(kMergeRows * D / 4) decode_merge(const Plan plan, const Args a) {
     constexpr int TPR = D / 4;
-    constexpr int U = 8;
+    constexpr int U = WAYS == 1 ? 8 : 4;
+    constexpr int ROWS = kMergeRows / WAYS;   // query heads per block
     const int CB = dec_col_blocks(a.group), HH = HW / CB;
     const int n_hg = (a.hkv + HH - 1) / HH;
     const Group g = group_of<true>(plan, blockIdx.x);
     if (g.n_split <= 1) return;
-    const int qh = ((int)blockIdx.x - g.merge_base) * kMergeRows + (int)threadIdx.x / TPR;
-    const int q4 = (int)threadIdx.x % TPR;
+    const int sub = (int)threadIdx.x / TPR, q4 = (int)threadIdx.x % TPR;
+    const int qh = ((int)blockIdx.x - g.merge_base) * ROWS + (WAYS == 1 ? sub : 0);
     if (qh >= a.hq) return;
     const int kvh = qh / a.group, c = qh - kvh * a.group;
     // the decode kernel's row of this query head: its wave (KV head slot x CB +
@@ -2068,34 +2124,37 @@ __global__ void __launch_bounds__(kMergeRows * D / 4) decode_merge(const Plan pl
     const int hg = kvh / HH, prow = ((kvh % HH) * CB + c / 16) * 16 + c % 16;
     const int L = g.tok0 + 1;
     const int n_live = min(g.n_split, (L - g.win + g.split_keys - 1) / g.split_keys);   // non-empty splits
-    float M = kNegBig, den = 0.f;
-    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int s0 = 0; s0 < n_live; s0 += U) {
+    Merged r;
+    for (int s0 = WAYS == 1 ? 0 : sub; s0 < n_live; s0 += U * WAYS) {
         float2 ml[U];
         float4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const size_t slot = (size_t)g.part_base + (size_t)min(s0 + u, n_live - 1) * n_hg + hg;
+            const size_t slot = (size_t)g.part_base + (size_t)min(s0 + u * WAYS, n_live - 1) * n_hg + hg;
             ml[u] = *reinterpret_cast<const float2*>(a.part_ml + (slot * kTileRows + prow) * 2);
             v[u] = *reinterpret_cast<const float4*>(a.part_o + (slot * kTileRows + prow) * D + q4 * 4);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s0 + u >= n_live) break;
-            const float m_new = fmaxf(M, ml[u].x);
-            const float c_old = __builtin_amdgcn_exp2f(M - m_new), c_new = __builtin_amdgcn_exp2f(ml[u].x - m_new);
-            num.x = num.x * c_old + c_new * v[u].x;
-            num.y = num.y * c_old + c_new * v[u].y;
-            num.z = num.z * c_old + c_new * v[u].z;
-            num.w = num.w * c_old + c_new * v[u].w;
-            den = den * c_old + c_new * ml[u].y;
-            M = m_new;
+            if (s0 + u * WAYS >= n_live) break;
+            r.add(ml[u].x, ml[u].y, v[u]);
         }
     }
-    const float inv = 1.f / den;
+    if constexpr (WAYS > 1) {
+        __shared__ float4 num[WAYS][TPR];
+        __shared__ float2 ml[WAYS];
+        num[sub][q4] = r.num;
+        if (q4 == 0) ml[sub] = make_float2(r.M, r.den);
+        __syncthreads();
+        if (sub > 0) return;
+#pragma unroll
+        for (int w = 1; w < WAYS; ++w)
+            if (w < n_live) r.add(ml[w].x, ml[w].y, num[w][q4]);
+    }
+    const float inv = 1.f / r.den;
     uint32_t* op = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.o) + ((size_t)g.q_row0 * a.hq + qh) * D + q4 * 4);
-    op[0] = pack_bf16(num.x * inv, num.y * inv);
-    op[1] = pack_bf16(num.z * inv, num.w * inv);
+    op[0] = pack_bf16(r.num.x * inv, r.num.y * inv);
+    op[1] = pack_bf16(r.num.z * inv, r.num.w * inv);
 }
 
 // ---------------------------------------------------------------------------------
@@ -2494,12 +2553,15 @@ hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args&
 }
 
 template <int D, int STYLE, bool ROPE, bool TABLE, int HW>
-hipError_t launch_dec_w(const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_dec_w(int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
     hipLaunchKernelGGL((decode_bf16<D, STYLE, ROPE, TABLE, HW>), dim3(plan.n_items), dim3(HW * 64), 0, st, plan, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (plan.n_merge > 0) {
-        hipLaunchKernelGGL((decode_merge<D, HW>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
+        if (merge_ways == 1)
+            hipLaunchKernelGGL((decode_merge<D, HW, 1>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
+        else
+            hipLaunchKernelGGL((decode_merge<D, HW, kMergeRows>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
         e = hipGetLastError();
     }
     return e;
@@ -2507,10 +2569,10 @@ hipError_t launch_dec_w(const Plan& plan, const Args& a, hipStream_t st) {
 
 // decode at the workgroup width the host plan assumed (dec_waves)
 template <int D, int STYLE, bool ROPE, bool TABLE>
-hipError_t launch_dec_t(const Plan& plan, const Args& a, hipStream_t st) {
-    if (dec_waves(D, a.hkv, a.group) == 2) return launch_dec_w<D, STYLE, ROPE, TABLE, 2>(plan, a, st);
-    if (dec_waves(D, a.hkv, a.group) == 4) return launch_dec_w<D, STYLE, ROPE, TABLE, 4>(plan, a, st);
-    return launch_dec_w<D, STYLE, ROPE, TABLE, dec_heads(D)>(plan, a, st);
+hipError_t launch_dec_t(int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
+    if (dec_waves(D, a.hkv, a.group) == 2) return launch_dec_w<D, STYLE, ROPE, TABLE, 2>(merge_ways, plan, a, st);
+    if (dec_waves(D, a.hkv, a.group) == 4) return launch_dec_w<D, STYLE, ROPE, TABLE, 4>(merge_ways, plan, a, st);
+    return launch_dec_w<D, STYLE, ROPE, TABLE, dec_heads(D)>(merge_ways, plan, a, st);
 }
 
 template <int D, int STYLE>
@@ -2523,10 +2585,10 @@ hipError_t launch_rope_keys_d(const KeyPlan& plan, const Args& a, hipStream_t st
 }
 
 template <int D, int STYLE>
-hipError_t launch_dec_d(bool rope, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_dec_d(bool rope, int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
     const bool table = a.rope_table != nullptr && a.rope_len > 0;
-    if (!rope) return launch_dec_t<D, STYLE, false, false>(plan, a, st);
-    return table ? launch_dec_t<D, STYLE, true, true>(plan, a, st) : launch_dec_t<D, STYLE, true, false>(plan, a, st);
+    if (!rope) return launch_dec_t<D, STYLE, false, false>(merge_ways, plan, a, st);
+    return table ? launch_dec_t<D, STYLE, true, true>(merge_ways, plan, a, st) : launch_dec_t<D, STYLE, true, false>(merge_ways, plan, a, st);
 }
 
 template <int D, int STYLE>
@@ -2601,25 +2663,25 @@ int launch_rope_table(int dtype, int d, const RopeSteps& steps, int n_pos, float
 
 int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x, int n,
                        int heads, const int32_t* positions, void* stream) {
-    const int64_t n_pairs = (int64_t)n * heads * (d / 2);
-    if (n_pairs == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n_pairs + 255) / 256));
+    const int64_t n_units = (int64_t)n * heads * (d / 16);
+    if (n_units == 0) return hipSuccess;
+    const dim3 grid((unsigned)((n_units + 255) / 256));
     const void* t = table;
     hipStream_t st = (hipStream_t)stream;
     if (dtype == 1) {
         if (style == kNeox)
             hipLaunchKernelGGL((rope_rotate_kernel<float, 0>), grid, dim3(256), 0, st, static_cast<float*>(x),
-                               n_pairs, heads, d, rot_half, steps, positions, t, rope_len);
+                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
         else
             hipLaunchKernelGGL((rope_rotate_kernel<float, 1>), grid, dim3(256), 0, st, static_cast<float*>(x),
-                               n_pairs, heads, d, rot_half, steps, positions, t, rope_len);
+                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
     } else {
         if (style == kNeox)
             hipLaunchKernelGGL((rope_rotate_kernel<__bf16, 0>), grid, dim3(256), 0, st, static_cast<__bf16*>(x),
-                               n_pairs, heads, d, rot_half, steps, positions, t, rope_len);
+                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
         else
             hipLaunchKernelGGL((rope_rotate_kernel<__bf16, 1>), grid, dim3(256), 0, st, static_cast<__bf16*>(x),
-                               n_pairs, heads, d, rot_half, steps, positions, t, rope_len);
+                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
     }
     return hipGetLastError();
 }
@@ -2636,12 +2698,12 @@ int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, vo
     return style == kNeox ? launch_rope_keys_d<128, 0>(plan, args, st) : launch_rope_keys_d<128, 1>(plan, args, st);
 }
 
-int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
+int launch_decode(int style, int d, bool rope, int merge_ways, const Plan& plan, const Args& args, void* stream) {
     if (plan.n_items == 0) return hipSuccess;
     hipStream_t st = (hipStream_t)stream;
     if (d == 64)
-        return style == kNeox ? launch_dec_d<64, 0>(rope, plan, args, st) : launch_dec_d<64, 1>(rope, plan, args, st);
-    return style == kNeox ? launch_dec_d<128, 0>(rope, plan, args, st) : launch_dec_d<128, 1>(rope, plan, args, st);
+        return style == kNeox ? launch_dec_d<64, 0>(rope, merge_ways, plan, args, st) : launch_dec_d<64, 1>(rope, merge_ways, plan, args, st);
+    return style == kNeox ? launch_dec_d<128, 0>(rope, merge_ways, plan, args, st) : launch_dec_d<128, 1>(rope, merge_ways, plan, args, st);
 }
 
 int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
