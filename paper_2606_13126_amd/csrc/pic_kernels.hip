@@ -2182,13 +2182,14 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     constexpr int TK = f32_tile_keys(NW);
     constexpr int HALF = D / 2;
     constexpr int KC = D / 16;            // 16-dim contraction steps of 4 products each
+    constexpr int LV = D == 128 ? 4 : 3;  // levels of the tree over the D / 8 chains of a score
     constexpr int DB = D / 16;            // 16-dim blocks of O^T
     constexpr int CH = D / 4;             // 16-byte chunks per row
     constexpr int KB = TK / 16;           // 16-key blocks per tile
     constexpr int TPK = NW * 64 / TK;     // staging threads per key
     constexpr int KU = D / 8 / TPK;       // staged K units (two chunks, four pairs) per thread
     constexpr int VU = CH / TPK;          // staged V chunks per thread
-    static_assert(KU >= 1 && VU >= 1 && TPK * KU * 8 == D, "staging shape");
+    static_assert(KU >= 1 && VU >= 1 && TPK * KU * 8 == D && 8 << LV == D, "staging shape");
 
     __shared__ f32x4v_t ks[TK * CH];
     __shared__ f32x4v_t vs[TK * CH];
@@ -2369,20 +2370,41 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
         }
         const int kt = kv_lo + t * TK;
         if (wave_live && kt <= g.tok0 + (min(wave_row0 + 15, row_hi - 1)) / G) {
-            f32x4v_t s[KB];
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) s[kb] = f32x4v_t{0.f, 0.f, 0.f, 0.f};
+            // 8 dimensions per chain, the chains summed as a binary tree (tree[kb][l]: 2^l of
+            // them): one chain over all dimensions rounds its growing sum D times, which
+            // alone put the outputs 1.4-1.7x further from 64 bits than a lane-by-lane sum
+            f32x4v_t tree[KB][LV + 1];
 #pragma unroll
             for (int c = 0; c < KC; ++c) {
                 f32x4v_t k[KB];
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb) k[kb] = ks[(16 * kb + c16) * CH + ((4 * c + q4) ^ c16)];
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int h = 0; h < 2; ++h) {
+                    f32x4v_t x[KB];
 #pragma unroll
-                    for (int kb = 0; kb < KB; ++kb)
-                        s[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[kb][e], q[c][e], s[kb], 0, 0, 0);
+                    for (int e = 2 * h; e < 2 * h + 2; ++e)
+#pragma unroll
+                        for (int kb = 0; kb < KB; ++kb)
+                            x[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(k[kb][e], q[c][e], e & 1 ? x[kb] : f32x4v_t{0.f, 0.f, 0.f, 0.f},
+                                                                         0, 0, 0);
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb) {
+                        const int n = 2 * c + h;
+#pragma unroll
+                        for (int l = 0; l <= LV; ++l) {
+                            if (((n >> l) & 1) == 0) {
+                                tree[kb][l] = x[kb];
+                                break;
+                            }
+                            x[kb] = tree[kb][l] + x[kb];
+                        }
+                    }
+                }
             }
+            f32x4v_t s[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) s[kb] = tree[kb][LV];
             const bool masked = kt + TK > kv_hi || kt + TK - 1 > wave_tmin;
             if (masked) {
 #pragma unroll
@@ -2454,14 +2476,14 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     const float lt = sum_xor32(sum_xor16(l_run));
     if (!row_valid) return;
     float* dst;
-    float inv = 1.f;
+    float den = 1.f;
     if (g.n_split > 1) {
         const size_t prow = ((size_t)g.part_base + (size_t)ic.cluster * n_rt + ic.rt) * (NW * 16) + wave * 16 + c16;
         dst = a.part_o + prow * D;
         if (q4 == 0) *reinterpret_cast<float2*>(a.part_ml + prow * 2) = make_float2(m_run, lt);
     } else {
         dst = static_cast<float*>(a.o) + ((size_t)(g.q_row0 + toff) * a.hq + qh) * D;
-        inv = 1.f / lt;
+        den = lt;
     }
 #pragma unroll
     for (int h = 0; h < DB / 4; ++h)
@@ -2469,7 +2491,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
         for (int i = 0; i < 4; ++i) {
             f32x4v_t w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = acc[4 * h + e][i] * inv;
+            for (int e = 0; e < 4; ++e) w[e] = acc[4 * h + e][i] / den;
             *reinterpret_cast<f32x4v_t*>(dst + 64 * h + 16 * q4 + 4 * i) = w;
         }
 }
@@ -2515,7 +2537,7 @@ __global__ void __launch_bounds__(kMergeRows * D / 4) merge_f32(const Plan plan,
     const int toff = row / G;
     *reinterpret_cast<f32x4v_t*>(static_cast<float*>(a.o) +
                                  ((size_t)(g.q_row0 + toff) * a.hq + (size_t)kvh * G + (row - toff * G)) * D + c4 * 4) =
-        num * (1.f / den);
+        num / den;
 }
 
 template <int D, int STYLE, bool ROPE, bool TABLE, int NW>
