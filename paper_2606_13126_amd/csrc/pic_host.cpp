@@ -119,7 +119,7 @@ struct HostPlan {
     int64_t n_parts = 0;       // split partial slots
     int64_t n_merge = 0;       // blocks of the merge launch
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
-    int merge_ways = 1;        // thread rows that share a query head's splits in the decode merge (1 or kMergeRows)
+    int merge_ways = 1;        // thread rows that share a query head's splits in the decode merge (1, kMergeRows or kMergeWays)
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
     pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
@@ -134,9 +134,9 @@ int64_t dec_head_groups(const pic_config* c) {
 }
 
 // Groups, their split policy and bases.  Prefill and float32 groups hold (row tile,
-// KV head, split) items.  `split_f32` false keeps float32 keys unsplit (for a
-// workspace without room for partials).
-pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool split_f32, HostPlan& hp) {
+// KV head, split) items.  `fine_splits` false (for a workspace without room for their
+// partials) keeps float32 keys unsplit and decode chunks at 4 cache blocks or more.
+pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool fine_splits, HostPlan& hp) {
     hp.groups.clear();
     hp.n_parts = 0;
     const int G = c->num_q_heads / c->num_kv_heads;
@@ -178,20 +178,30 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
     if (hp.dec_kernel) {
         // Decode items are (request, key split, group of KV heads).  A wide workgroup
         // holds a CU (narrow ones share it three or two ways), so cut the keys into
-        // chunks of about the average work per resident workgroup (at least 4 cache
-        // blocks) and balance the splits of each request.
+        // chunks of about the average work per resident workgroup and balance the splits
+        // of each request.  A chunk has at least 2 cache blocks while that makes at most
+        // kMaxEightWays splits, 4 otherwise: decode + merge, 4 against 2 blocks, one request
+        // of 1,537 keys 15.3 against 14.2 us, of 500 keys 15.0 against 12.0; two of 3,000
+        // keys 17.1 against 17.3 (94 splits), one of 9,000 keys of 4 KV heads 19.6 against
+        // 27.1 (282 splits), both merged eight ways.
         const int64_t n_hg = dec_head_groups(c);
-        int64_t tiles_total = 0;
-        for (auto& g : hp.groups)
-            tiles_total += n_hg * (((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys);
+        int64_t tiles_total = 0, longest = 0;
+        for (auto& g : hp.groups) {
+            const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
+            tiles_total += n_hg * tiles;
+            longest = std::max(longest, tiles);
+        }
+        const int64_t least = fine_splits && longest <= 2 * pic::kMaxEightWays ? 2 : 4;
         const int64_t target = (int64_t)pic::kTargetCUs * pic::dec_wgs_per_cu(pic::dec_waves(c->head_dim, c->num_kv_heads, G));
-        const int64_t chunk = std::max<int64_t>(4, (tiles_total + target - 1) / target);
+        const int64_t chunk = std::max(least, (tiles_total + target - 1) / target);
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
             g.split_keys = (int32_t)(((tiles + g.n_split - 1) / g.n_split) * pic::kDecTileKeys);
-            // a merge block loads up to 8 splits at once; more of them go eight ways
-            if (g.n_split > 8) hp.merge_ways = pic::kMergeRows;
+            // a merge thread loads up to 8 splits at once: more of them go eight ways, and
+            // more than eight threads load at once thirty-two ways
+            const int ways = g.n_split > pic::kMaxEightWays ? pic::kMergeWays : g.n_split > 8 ? pic::kMergeRows : 1;
+            hp.merge_ways = std::max(hp.merge_ways, ways);
         }
         std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
             return std::min<int64_t>(x.split_keys, x.tok0 + 1 - x.win) > std::min<int64_t>(y.split_keys, y.tok0 + 1 - y.win);
@@ -220,7 +230,7 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
                 tiles_total += ((int64_t)g.tok0 + (std::min((rt + 1) * tr, (int64_t)g.n_tok * G) - 1) / G - g.win + tk) / tk *
                                c->num_kv_heads;
         }
-        const int64_t chunk = split_f32 && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
+        const int64_t chunk = fine_splits && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
                                                              : (int64_t)INT32_MAX;
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + tk - 1) / tk;
@@ -283,7 +293,7 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
         if (hp.dec_kernel) {
             if (g.n_split > 1) {
                 part += n;
-                const int64_t rows = pic::kMergeRows / hp.merge_ways;   // query heads per block
+                const int64_t rows = hp.merge_ways == 1 ? pic::kMergeRows : 1;   // query heads per block
                 merge += (c->num_q_heads + rows - 1) / rows;
             }
         } else if (g.n_split > 1) {
@@ -389,18 +399,18 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
 }
 
 // The plan of a call: groups with their split policy, then their bases.
-pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool split_f32 = true) {
-    pic_status st = make_plan(c, b, decode, split_f32, hp);
+pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool fine_splits = true) {
+    pic_status st = make_plan(c, b, decode, fine_splits, hp);
     if (st) return st;
     plan_keys(c, hp);
     return assign_bases(c, hp);
 }
 
-// The plan of a call with ws_bytes of workspace: float32 keys stay unsplit where the
-// partials do not fit (a workspace of the size an unsplit plan needs is enough).
+// The plan of a call with ws_bytes of workspace: splits that a call can do without are
+// left out where their partials do not fit.
 pic_status build_plan_within(const pic_config* c, const pic_batch_host* b, bool decode, size_t ws_bytes, HostPlan& hp) {
     pic_status st = build_plan(c, b, decode, hp);
-    if (st == PIC_OK && c->dtype == PIC_F32 && hp.n_parts > 0 && ws_layout(c, hp).total > ws_bytes) {
+    if (st == PIC_OK && (decode || c->dtype == PIC_F32) && hp.n_parts > 0 && ws_layout(c, hp).need > ws_bytes) {
         hp = HostPlan{};
         st = build_plan(c, b, decode, hp, false);
     }

@@ -21,6 +21,8 @@ constexpr int kMaxGroups = 64;    // groups passed by value as a kernel argument
 constexpr int kUploadGroups = 80; // groups carried by one plan-upload launch
 constexpr int kTargetCUs = 256;   // MI355X compute units the split policy fills
 constexpr int kMergeRows = 8;     // rows per block of the split merge
+constexpr int kMergeWays = 32;    // thread rows of a decode merge of very many splits
+constexpr int kMaxEightWays = 64; // splits that eight thread rows load in one round
 constexpr int kDecTileKeys = 16;  // keys per decode tile (one cache block)
 constexpr int kDecMaxG = 64;      // query heads per KV head the decode kernel handles
 #ifndef PIC_DEC_HEADS_D128

@@ -2102,15 +2102,18 @@ struct Merged {
 
 // decode merge: one float4 of a query head's row per thread.  WAYS = 1: a block per
 // (request, kMergeRows query heads), the (max, sum) pairs and partial rows of up to 8
-// splits loaded together before they are combined.  WAYS = 8, for more splits than
-// that: a block per query head, whose eight thread rows take every eighth split (four
-// loads in flight each) and meet in LDS.  Bound by the round trips of its loads: 25
-// splits of one request take 4.8 us in eight ways, 10.5 us one after another.
+// splits loaded together before they are combined.  WAYS = 8 or 32, for more splits than
+// that: a block per query head, whose thread rows take every WAYS-th split (eight loads
+// in flight each) and meet in LDS.  Bound by the round trips of its loads: 25 splits of
+// one request take 4.8 us in eight ways, 10.5 us one after another; 235 splits 8.1 us in
+// thirty-two ways, 14.3 us in eight.
+constexpr int decode_merge_rows(int ways) { return ways == 1 ? kMergeRows : ways; }
+
 template <int D, int HW, int WAYS>
-__global__ void __launch_bounds__(kMergeRows * D / 4) decode_merge(const Plan plan, const Args a) {
+__global__ void __launch_bounds__(decode_merge_rows(WAYS) * D / 4) decode_merge(const Plan plan, const Args a) {
     constexpr int TPR = D / 4;
-    constexpr int U = WAYS == 1 ? 8 : 4;
-    constexpr int ROWS = kMergeRows / WAYS;   // query heads per block
+    constexpr int U = 8;
+    constexpr int ROWS = WAYS == 1 ? kMergeRows : 1;   // query heads per block
     const int CB = dec_col_blocks(a.group), HH = HW / CB;
     const int n_hg = (a.hkv + HH - 1) / HH;
     const Group g = group_of<true>(plan, blockIdx.x);
@@ -2581,9 +2584,13 @@ hipError_t launch_dec_w(int merge_ways, const Plan& plan, const Args& a, hipStre
     if (e != hipSuccess) return e;
     if (plan.n_merge > 0) {
         if (merge_ways == 1)
-            hipLaunchKernelGGL((decode_merge<D, HW, 1>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
+            hipLaunchKernelGGL((decode_merge<D, HW, 1>), dim3(plan.n_merge), dim3(decode_merge_rows(1) * D / 4), 0, st, plan, a);
+        else if (merge_ways == kMergeRows)
+            hipLaunchKernelGGL((decode_merge<D, HW, kMergeRows>), dim3(plan.n_merge), dim3(decode_merge_rows(kMergeRows) * D / 4), 0, st,
+                               plan, a);
         else
-            hipLaunchKernelGGL((decode_merge<D, HW, kMergeRows>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
+            hipLaunchKernelGGL((decode_merge<D, HW, kMergeWays>), dim3(plan.n_merge), dim3(decode_merge_rows(kMergeWays) * D / 4), 0, st,
+                               plan, a);
         e = hipGetLastError();
     }
     return e;
