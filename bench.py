@@ -390,7 +390,7 @@ def main():
                    "step": "pic_kv_write(16,896 rows) + pic_attn_prefill"},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_BF16_TFLOPS, "traffic": measured_traffic(),
-                     "kernel": "pic_attn_prefill call (prefill_bf16 + split merge)", "avg_ms": attn_avg,
+                     "kernel": "pic_attn_prefill call (rope_keys + prefill_direct + split merge)", "avg_ms": attn_avg,
                      "flops_per_call": flops},
     }
     del db
