@@ -2176,7 +2176,7 @@ __global__ void __launch_bounds__(decode_merge_rows(WAYS) * D / 4) decode_merge(
 // read of a V row serves four blocks and the output leaves in 16-byte stores.
 // Bound by the matrix cores: 8 D flops per (row, key) at 64 flops per cycle and SIMD;
 // one wave per (token, head) with a shuffle sum per key took 638 us on 573 queries of
-// 8 heads over up to 1,400 keys (1 TFLOP/s), this form takes 24 us (26 TFLOP/s).
+// 8 heads over up to 1,400 keys (1 TFLOP/s), this form takes 25.5 us (24 TFLOP/s).
 // ---------------------------------------------------------------------------------
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 
