@@ -185,9 +185,9 @@ pic_status pic_blocks_scatter(const pic_config* cfg, void* k_pool, void* v_pool,
  * and, for batches of more than 64 groups (query spans; requests for decode), the
  * work-group table that the call writes there before its attention launch; for a
  * prefill whose keys are shared by many query rows also room for a rotated copy of
- * those keys (at most 256 MiB).  The copy, the partial results of float32 calls and those
- * of decode chunks under four cache blocks are optional: a workspace without room for
- * them is accepted, and the call is slower.  May be 0.  Returned through *bytes (the status reports argument errors). */
+ * those keys (at most 256 MiB).  The copy, and the partial results of float32 calls,
+ * are optional: a workspace without room for them is accepted, and the call is slower.
+ * May be 0.  Returned through *bytes (the status reports argument errors). */
 pic_status pic_workspace_size(const pic_config* cfg, const pic_batch_host* batch, int32_t is_decode,
                               size_t* bytes);
 

@@ -134,9 +134,9 @@ int64_t dec_head_groups(const pic_config* c) {
 }
 
 // Groups, their split policy and bases.  Prefill and float32 groups hold (row tile,
-// KV head, split) items.  `fine_splits` false (for a workspace without room for their
-// partials) keeps float32 keys unsplit and decode chunks at 4 cache blocks or more.
-pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool fine_splits, HostPlan& hp) {
+// KV head, split) items.  `split_f32` false (for a workspace without room for their
+// partials) keeps float32 keys unsplit.
+pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool split_f32, HostPlan& hp) {
     hp.groups.clear();
     hp.n_parts = 0;
     const int G = c->num_q_heads / c->num_kv_heads;
@@ -178,22 +178,18 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
     if (hp.dec_kernel) {
         // Decode items are (request, key split, group of KV heads).  A wide workgroup
         // holds a CU (narrow ones share it three or two ways), so cut the keys into
-        // chunks of about the average work per resident workgroup and balance the splits
-        // of each request.  A chunk has at least 2 cache blocks while that makes at most
-        // kMaxEightWays splits, 4 otherwise: decode + merge, 4 against 2 blocks, one request
-        // of 1,537 keys 15.3 against 14.2 us, of 500 keys 15.0 against 12.0; two of 3,000
-        // keys 17.1 against 17.3 (94 splits), one of 9,000 keys of 4 KV heads 19.6 against
-        // 27.1 (282 splits), both merged eight ways.
+        // chunks of about the average work per resident workgroup (at least 4 cache
+        // blocks) and balance the splits of each request.  Finer chunks are faster (decode +
+        // merge, 4 against 2 blocks: one request of 1,537 keys 15.3 against 14.2 us, of 500
+        // keys 15.0 against 12.0) but less exact: a split rounds its probabilities to bf16
+        // relative to its own running maximum, and one request of 1,537 keys is 3.84e-3 from
+        // 64 bits in chunks of 2 blocks, 3.72e-3 in chunks of 4.
         const int64_t n_hg = dec_head_groups(c);
-        int64_t tiles_total = 0, longest = 0;
-        for (auto& g : hp.groups) {
-            const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
-            tiles_total += n_hg * tiles;
-            longest = std::max(longest, tiles);
-        }
-        const int64_t least = fine_splits && longest <= 2 * pic::kMaxEightWays ? 2 : 4;
+        int64_t tiles_total = 0;
+        for (auto& g : hp.groups)
+            tiles_total += n_hg * (((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys);
         const int64_t target = (int64_t)pic::kTargetCUs * pic::dec_wgs_per_cu(pic::dec_waves(c->head_dim, c->num_kv_heads, G));
-        const int64_t chunk = std::max(least, (tiles_total + target - 1) / target);
+        const int64_t chunk = std::max<int64_t>(4, (tiles_total + target - 1) / target);
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
@@ -230,8 +226,8 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
                 tiles_total += ((int64_t)g.tok0 + (std::min((rt + 1) * tr, (int64_t)g.n_tok * G) - 1) / G - g.win + tk) / tk *
                                c->num_kv_heads;
         }
-        const int64_t chunk = fine_splits && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
-                                                             : (int64_t)INT32_MAX;
+        const int64_t chunk = split_f32 && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
+                                                           : (int64_t)INT32_MAX;
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + tk - 1) / tk;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
@@ -399,18 +395,18 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
 }
 
 // The plan of a call: groups with their split policy, then their bases.
-pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool fine_splits = true) {
-    pic_status st = make_plan(c, b, decode, fine_splits, hp);
+pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool split_f32 = true) {
+    pic_status st = make_plan(c, b, decode, split_f32, hp);
     if (st) return st;
     plan_keys(c, hp);
     return assign_bases(c, hp);
 }
 
-// The plan of a call with ws_bytes of workspace: splits that a call can do without are
-// left out where their partials do not fit.
+// The plan of a call with ws_bytes of workspace: float32 key splits, which a call can do
+// without, are left out where their partials do not fit.
 pic_status build_plan_within(const pic_config* c, const pic_batch_host* b, bool decode, size_t ws_bytes, HostPlan& hp) {
     pic_status st = build_plan(c, b, decode, hp);
-    if (st == PIC_OK && (decode || c->dtype == PIC_F32) && hp.n_parts > 0 && ws_layout(c, hp).need > ws_bytes) {
+    if (st == PIC_OK && c->dtype == PIC_F32 && hp.n_parts > 0 && ws_layout(c, hp).need > ws_bytes) {
         hp = HostPlan{};
         st = build_plan(c, b, decode, hp, false);
     }

@@ -273,6 +273,18 @@ def test_plan_exact_cover_explicit_windows(dtype):
     assert check_exact_cover(windows_decode_case(), dtype, True) == 2 * 32
 
 
+@pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 2, 64), (4, 1, 128), (12, 12, 64)])
+@pytest.mark.parametrize("keys", [33, 64, 65, 500, 1537, 2048])
+def test_decode_chunks_hold_four_cache_blocks(Hq, Hkv, D, keys):
+    # finer chunks round more probabilities relative to the maximum of a few keys: their
+    # outputs are further from 64 bits
+    hb = B.HostBatch([keys], [0, 1], [0], [W.PDEP])
+    items = P.pic_plan_debug(P.make_config(Hq, Hkv, D), hb, True)
+    splits = {(int(it[4]), int(it[5])) for it in items}
+    blocks = -(-keys // 16)
+    assert len(splits) == -(-blocks // 4), sorted(splits)
+
+
 # ---- batches with more groups than the kernel arguments hold ----------------------------
 
 @pytest.mark.parametrize("dtype", [B.PIC_BF16, B.PIC_F32])

@@ -1,5 +1,5 @@
-"""GPU: decode at the edges of its split policy and of the three forms of its merge (up to
-8 splits, up to 64, more), with and without the scratch that the finest splits need."""
+"""GPU: decode at the edges of its split policy (chunks of four cache blocks) and of the
+three forms of its merge (up to 8 splits, up to 64, more)."""
 import pytest
 import torch
 
@@ -20,11 +20,14 @@ def _gpu():
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,lens", [
-    (8, 2, 128, [32]),             # 33 keys: three cache blocks in chunks of two
-    (8, 8, 64, [255]),             # 16 blocks: eight splits, merged by one thread row
-    (4, 1, 128, [256, 5]),         # 17 blocks: nine splits, eight thread rows
-    (32, 8, 128, [2047]),          # 128 blocks: 64 splits
-    (8, 2, 64, [2048, 300]),       # 129 blocks: chunks of four
+    (8, 2, 128, [32]),             # 33 keys: three cache blocks, unsplit
+    (8, 8, 64, [255]),             # 16 blocks: four splits
+    (4, 1, 128, [256, 5]),         # 17 blocks: five splits of up to four blocks, and one request unsplit
+    (8, 8, 64, [511]),             # 32 blocks: eight splits, merged by one thread row
+    (4, 1, 128, [512, 5]),         # 33 blocks: nine splits, eight thread rows
+    (32, 8, 128, [2047]),          # 128 blocks: 32 splits
+    (8, 2, 64, [2048, 300]),       # 129 and 19 blocks: 33 and 5 splits
+    (32, 8, 128, [4095]),          # 256 blocks: 64 splits
     (28, 4, 128, [4096, 40]),      # 257 blocks: 65 splits, thirty-two thread rows
     (12, 12, 64, [6000]),          # 94 splits of heads that fill two workgroups
 ])
@@ -37,7 +40,7 @@ def test_decode_split_and_merge_edges(Hq, Hkv, D, lens):
     ref = WO.run(wl)
     assert_close(to_np(db.o), ref, wl.dtype, wl.name)
     if lens[0] < 256 and D == 128:
-        # a workspace of what chunks of four blocks need (none for 33 keys): still accepted
+        # an unsplit call needs no workspace
         db.workspace = None
         db.o.fill_(float("nan"))
         db.attend()
