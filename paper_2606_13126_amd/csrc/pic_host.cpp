@@ -119,7 +119,7 @@ struct HostPlan {
     int64_t n_parts = 0;       // split partial slots
     int64_t n_merge = 0;       // blocks of the merge launch
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
-    int merge_ways = 1;        // thread rows that share a query head's splits in the decode merge (1, kMergeRows or kMergeWays)
+    int merge_ways = 1;        // most thread rows that share a query head's splits in the decode merge
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
     pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
@@ -134,9 +134,9 @@ int64_t dec_head_groups(const pic_config* c) {
 }
 
 // Groups, their split policy and bases.  Prefill and float32 groups hold (row tile,
-// KV head, split) items.  `split_f32` false (for a workspace without room for their
-// partials) keeps float32 keys unsplit.
-pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool split_f32, HostPlan& hp) {
+// KV head, split) items.  `lean` (for a workspace without room for the rest) keeps
+// float32 keys unsplit and gives every query head of a decode merge one thread row.
+pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, bool lean, HostPlan& hp) {
     hp.groups.clear();
     hp.n_parts = 0;
     const int G = c->num_q_heads / c->num_kv_heads;
@@ -194,10 +194,7 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
             const int64_t tiles = ((int64_t)g.tok0 + 1 - g.win + pic::kDecTileKeys - 1) / pic::kDecTileKeys;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
             g.split_keys = (int32_t)(((tiles + g.n_split - 1) / g.n_split) * pic::kDecTileKeys);
-            // a merge thread loads up to 8 splits at once: more of them go eight ways, and
-            // more than eight threads load at once thirty-two ways
-            const int ways = g.n_split > pic::kMaxEightWays ? pic::kMergeWays : g.n_split > 8 ? pic::kMergeRows : 1;
-            hp.merge_ways = std::max(hp.merge_ways, ways);
+            if (!lean) hp.merge_ways = std::max(hp.merge_ways, pic::dec_merge_ways(g.n_split, pic::kMergeWays));
         }
         std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
             return std::min<int64_t>(x.split_keys, x.tok0 + 1 - x.win) > std::min<int64_t>(y.split_keys, y.tok0 + 1 - y.win);
@@ -226,8 +223,8 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
                 tiles_total += ((int64_t)g.tok0 + (std::min((rt + 1) * tr, (int64_t)g.n_tok * G) - 1) / G - g.win + tk) / tk *
                                c->num_kv_heads;
         }
-        const int64_t chunk = split_f32 && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
-                                                           : (int64_t)INT32_MAX;
+        const int64_t chunk = !lean && base < 2 * target ? std::max<int64_t>(128 / tk, (tiles_total + target - 1) / target)
+                                                       : (int64_t)INT32_MAX;
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + tk - 1) / tk;
             g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
@@ -289,8 +286,8 @@ pic_status assign_bases(const pic_config* c, HostPlan& hp) {
         if (hp.dec_kernel) {
             if (g.n_split > 1) {
                 part += n;
-                const int64_t rows = hp.merge_ways == 1 ? pic::kMergeRows : 1;   // query heads per block
-                merge += (c->num_q_heads + rows - 1) / rows;
+                const int64_t heads = pic::dec_merge_rows(hp.merge_ways) / pic::dec_merge_ways(g.n_split, hp.merge_ways);   // per block
+                merge += (c->num_q_heads + heads - 1) / heads;
             }
         } else if (g.n_split > 1) {
             const int64_t n_rt = pic::row_tiles(g, c->num_q_heads / c->num_kv_heads, hp.tile_rows());
@@ -395,20 +392,21 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
 }
 
 // The plan of a call: groups with their split policy, then their bases.
-pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool split_f32 = true) {
-    pic_status st = make_plan(c, b, decode, split_f32, hp);
+pic_status build_plan(const pic_config* c, const pic_batch_host* b, bool decode, HostPlan& hp, bool lean = false) {
+    pic_status st = make_plan(c, b, decode, lean, hp);
     if (st) return st;
     plan_keys(c, hp);
     return assign_bases(c, hp);
 }
 
-// The plan of a call with ws_bytes of workspace: float32 key splits, which a call can do
-// without, are left out where their partials do not fit.
+// The plan of a call with ws_bytes of workspace.  What a call can do without is left out
+// where it does not fit: float32 key splits (their partials) and the wider decode merges
+// (a merge block per query head, and in a large batch a map entry for each).
 pic_status build_plan_within(const pic_config* c, const pic_batch_host* b, bool decode, size_t ws_bytes, HostPlan& hp) {
     pic_status st = build_plan(c, b, decode, hp);
-    if (st == PIC_OK && c->dtype == PIC_F32 && hp.n_parts > 0 && ws_layout(c, hp).need > ws_bytes) {
+    if (st == PIC_OK && (c->dtype == PIC_F32 || hp.dec_kernel) && hp.n_parts > 0 && ws_layout(c, hp).need > ws_bytes) {
         hp = HostPlan{};
-        st = build_plan(c, b, decode, hp, false);
+        st = build_plan(c, b, decode, hp, true);
     }
     return st;
 }
@@ -528,6 +526,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     p.n_groups = (int32_t)hp.groups.size();
     p.n_items = (int32_t)hp.n_items;
     p.n_merge = (int32_t)hp.n_merge;
+    p.merge_ways = hp.merge_ways;
     if (hp.groups.size() <= (size_t)pic::kMaxGroups) {
         std::copy(hp.groups.begin(), hp.groups.end(), p.g);
     } else {
@@ -560,7 +559,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
         (st = hip_status(pic::launch_rope_keys(c->rope_style, c->head_dim, hp.keys, a, stream), "key rotation launch")))
         return st;
     const bool rope_on = c->k_prerotated == 0;
-    const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, hp.merge_ways, p, a, stream)
+    const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, p, a, stream)
                                 : pic::launch_attention(c->dtype, hp.f32_waves, c->rope_style, c->head_dim, rope_on, p, a, stream);
     return hip_status(e, "attention launch");
 }

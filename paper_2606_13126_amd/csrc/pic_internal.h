@@ -23,6 +23,16 @@ constexpr int kTargetCUs = 256;   // MI355X compute units the split policy fills
 constexpr int kMergeRows = 8;     // rows per block of the split merge
 constexpr int kMergeWays = 32;    // thread rows of a decode merge of very many splits
 constexpr int kMaxEightWays = 64; // splits that eight thread rows load in one round
+
+// Thread rows of the decode merge that share one query head's splits, at most `most` of
+// them (Plan::merge_ways): a thread loads up to 8 splits at once, so more of them go
+// eight ways, and more than eight threads load at once thirty-two ways.
+__host__ __device__ inline int dec_merge_ways(int n_split, int most) {
+    const int ways = n_split > kMaxEightWays ? kMergeWays : n_split > 8 ? kMergeRows : 1;
+    return ways < most ? ways : most;
+}
+// Thread rows of a decode merge block: the other rows take other query heads
+constexpr int dec_merge_rows(int most) { return most == kMergeWays ? kMergeWays : kMergeRows; }
 constexpr int kDecTileKeys = 16;  // keys per decode tile (one cache block)
 constexpr int kDecMaxG = 64;      // query heads per KV head the decode kernel handles
 #ifndef PIC_DEC_HEADS_D128
@@ -92,7 +102,7 @@ struct Plan {
     int32_t n_groups;
     int32_t n_items;     // blocks of the attention launch
     int32_t n_merge;     // blocks of the merge launch
-    int32_t pad_;
+    int32_t merge_ways;  // most thread rows per query head of a decode merge (1, kMergeRows or kMergeWays)
     const Group* table;       // device [n_groups], or null when g[] holds the groups
     const int32_t* item_map;  // device [n_items]: group of each attention block
     const int32_t* merge_map; // device [n_merge]: group of each merge block
@@ -185,7 +195,7 @@ int launch_blocks_copy(int dtype, int hkv, int d, void* k_pool, void* v_pool, vo
 int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x,
                        int n, int heads, const int32_t* positions, void* stream);
 int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
-int launch_decode(int style, int d, bool rope, int merge_ways, const Plan& plan, const Args& args, void* stream);
+int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, void* stream);
 int launch_plan_upload(const PlanUpload& up, void* stream);
 

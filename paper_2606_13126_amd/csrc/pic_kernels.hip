@@ -2100,27 +2100,24 @@ struct Merged {
     }
 };
 
-// decode merge: one float4 of a query head's row per thread.  WAYS = 1: a block per
-// (request, kMergeRows query heads), the (max, sum) pairs and partial rows of up to 8
-// splits loaded together before they are combined.  WAYS = 8 or 32, for more splits than
-// that: a block per query head, whose thread rows take every WAYS-th split (eight loads
-// in flight each) and meet in LDS.  Bound by the round trips of its loads: 25 splits of
-// one request take 4.8 us in eight ways, 10.5 us one after another; 235 splits 8.1 us in
-// thirty-two ways, 14.3 us in eight.
-constexpr int decode_merge_rows(int ways) { return ways == 1 ? kMergeRows : ways; }
-
-template <int D, int HW, int WAYS>
-__global__ void __launch_bounds__(decode_merge_rows(WAYS) * D / 4) decode_merge(const Plan plan, const Args a) {
+// decode merge: one float4 of a query head's row per thread, ROWS thread rows per block.
+// The splits of a query head are shared by `ways` of them (dec_merge_ways: 1, 8 or 32 by
+// the request's splits), each taking every ways-th split, eight loads in flight, and
+// meeting in LDS; the block's other rows take other query heads.  Bound by the round
+// trips of the loads: 25 splits of one request take 4.8 us in eight ways, 10.5 us one
+// after another; 235 splits 8.1 us in thirty-two ways, 14.3 us in eight.
+template <int D, int HW, int ROWS>
+__global__ void __launch_bounds__(ROWS * D / 4) decode_merge(const Plan plan, const Args a) {
     constexpr int TPR = D / 4;
     constexpr int U = 8;
-    constexpr int ROWS = WAYS == 1 ? kMergeRows : 1;   // query heads per block
     const int CB = dec_col_blocks(a.group), HH = HW / CB;
     const int n_hg = (a.hkv + HH - 1) / HH;
     const Group g = group_of<true>(plan, blockIdx.x);
     if (g.n_split <= 1) return;
+    const int ways = dec_merge_ways(g.n_split, plan.merge_ways);   // a power of two, at most ROWS
     const int sub = (int)threadIdx.x / TPR, q4 = (int)threadIdx.x % TPR;
-    const int qh = ((int)blockIdx.x - g.merge_base) * ROWS + (WAYS == 1 ? sub : 0);
-    if (qh >= a.hq) return;
+    const int qh = ((int)blockIdx.x - g.merge_base) * (ROWS / ways) + sub / ways, way = sub & (ways - 1);
+    const bool live = qh < a.hq;
     const int kvh = qh / a.group, c = qh - kvh * a.group;
     // the decode kernel's row of this query head: its wave (KV head slot x CB +
     // column block) times 16 plus its column
@@ -2128,32 +2125,34 @@ __global__ void __launch_bounds__(decode_merge_rows(WAYS) * D / 4) decode_merge(
     const int L = g.tok0 + 1;
     const int n_live = min(g.n_split, (L - g.win + g.split_keys - 1) / g.split_keys);   // non-empty splits
     Merged r;
-    for (int s0 = WAYS == 1 ? 0 : sub; s0 < n_live; s0 += U * WAYS) {
+    for (int s0 = way; live && s0 < n_live; s0 += U * ways) {
         float2 ml[U];
         float4 v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const size_t slot = (size_t)g.part_base + (size_t)min(s0 + u * WAYS, n_live - 1) * n_hg + hg;
+            const size_t slot = (size_t)g.part_base + (size_t)min(s0 + u * ways, n_live - 1) * n_hg + hg;
             ml[u] = *reinterpret_cast<const float2*>(a.part_ml + (slot * kTileRows + prow) * 2);
             v[u] = *reinterpret_cast<const float4*>(a.part_o + (slot * kTileRows + prow) * D + q4 * 4);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (s0 + u * WAYS >= n_live) break;
+            if (s0 + u * ways >= n_live) break;
             r.add(ml[u].x, ml[u].y, v[u]);
         }
     }
-    if constexpr (WAYS > 1) {
-        __shared__ float4 num[WAYS][TPR];
-        __shared__ float2 ml[WAYS];
+    if (ways > 1) {
+        __shared__ float4 num[ROWS][TPR];
+        __shared__ float2 ml[ROWS];
         num[sub][q4] = r.num;
         if (q4 == 0) ml[sub] = make_float2(r.M, r.den);
         __syncthreads();
-        if (sub > 0) return;
+        if (way > 0) return;
+        for (int w0 = 0; w0 < ways; w0 += 8)
 #pragma unroll
-        for (int w = 1; w < WAYS; ++w)
-            if (w < n_live) r.add(ml[w].x, ml[w].y, num[w][q4]);
+            for (int w = w0; w < w0 + 8; ++w)
+                if (w > 0 && w < n_live) r.add(ml[sub + w].x, ml[sub + w].y, num[sub + w][q4]);
     }
+    if (!live) return;
     const float inv = 1.f / r.den;
     uint32_t* op = reinterpret_cast<uint32_t*>(static_cast<uint16_t*>(a.o) + ((size_t)g.q_row0 * a.hq + qh) * D + q4 * 4);
     op[0] = pack_bf16(r.num.x * inv, r.num.y * inv);
@@ -2578,19 +2577,15 @@ hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args&
 }
 
 template <int D, int STYLE, bool ROPE, bool TABLE, int HW>
-hipError_t launch_dec_w(int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_dec_w(const Plan& plan, const Args& a, hipStream_t st) {
     hipLaunchKernelGGL((decode_bf16<D, STYLE, ROPE, TABLE, HW>), dim3(plan.n_items), dim3(HW * 64), 0, st, plan, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (plan.n_merge > 0) {
-        if (merge_ways == 1)
-            hipLaunchKernelGGL((decode_merge<D, HW, 1>), dim3(plan.n_merge), dim3(decode_merge_rows(1) * D / 4), 0, st, plan, a);
-        else if (merge_ways == kMergeRows)
-            hipLaunchKernelGGL((decode_merge<D, HW, kMergeRows>), dim3(plan.n_merge), dim3(decode_merge_rows(kMergeRows) * D / 4), 0, st,
-                               plan, a);
+        if (dec_merge_rows(plan.merge_ways) == kMergeRows)
+            hipLaunchKernelGGL((decode_merge<D, HW, kMergeRows>), dim3(plan.n_merge), dim3(kMergeRows * D / 4), 0, st, plan, a);
         else
-            hipLaunchKernelGGL((decode_merge<D, HW, kMergeWays>), dim3(plan.n_merge), dim3(decode_merge_rows(kMergeWays) * D / 4), 0, st,
-                               plan, a);
+            hipLaunchKernelGGL((decode_merge<D, HW, kMergeWays>), dim3(plan.n_merge), dim3(kMergeWays * D / 4), 0, st, plan, a);
         e = hipGetLastError();
     }
     return e;
@@ -2598,10 +2593,10 @@ hipError_t launch_dec_w(int merge_ways, const Plan& plan, const Args& a, hipStre
 
 // decode at the workgroup width the host plan assumed (dec_waves)
 template <int D, int STYLE, bool ROPE, bool TABLE>
-hipError_t launch_dec_t(int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
-    if (dec_waves(D, a.hkv, a.group) == 2) return launch_dec_w<D, STYLE, ROPE, TABLE, 2>(merge_ways, plan, a, st);
-    if (dec_waves(D, a.hkv, a.group) == 4) return launch_dec_w<D, STYLE, ROPE, TABLE, 4>(merge_ways, plan, a, st);
-    return launch_dec_w<D, STYLE, ROPE, TABLE, dec_heads(D)>(merge_ways, plan, a, st);
+hipError_t launch_dec_t(const Plan& plan, const Args& a, hipStream_t st) {
+    if (dec_waves(D, a.hkv, a.group) == 2) return launch_dec_w<D, STYLE, ROPE, TABLE, 2>(plan, a, st);
+    if (dec_waves(D, a.hkv, a.group) == 4) return launch_dec_w<D, STYLE, ROPE, TABLE, 4>(plan, a, st);
+    return launch_dec_w<D, STYLE, ROPE, TABLE, dec_heads(D)>(plan, a, st);
 }
 
 template <int D, int STYLE>
@@ -2614,10 +2609,10 @@ hipError_t launch_rope_keys_d(const KeyPlan& plan, const Args& a, hipStream_t st
 }
 
 template <int D, int STYLE>
-hipError_t launch_dec_d(bool rope, int merge_ways, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_dec_d(bool rope, const Plan& plan, const Args& a, hipStream_t st) {
     const bool table = a.rope_table != nullptr && a.rope_len > 0;
-    if (!rope) return launch_dec_t<D, STYLE, false, false>(merge_ways, plan, a, st);
-    return table ? launch_dec_t<D, STYLE, true, true>(merge_ways, plan, a, st) : launch_dec_t<D, STYLE, true, false>(merge_ways, plan, a, st);
+    if (!rope) return launch_dec_t<D, STYLE, false, false>(plan, a, st);
+    return table ? launch_dec_t<D, STYLE, true, true>(plan, a, st) : launch_dec_t<D, STYLE, true, false>(plan, a, st);
 }
 
 template <int D, int STYLE>
@@ -2727,12 +2722,12 @@ int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, vo
     return style == kNeox ? launch_rope_keys_d<128, 0>(plan, args, st) : launch_rope_keys_d<128, 1>(plan, args, st);
 }
 
-int launch_decode(int style, int d, bool rope, int merge_ways, const Plan& plan, const Args& args, void* stream) {
+int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
     if (plan.n_items == 0) return hipSuccess;
     hipStream_t st = (hipStream_t)stream;
     if (d == 64)
-        return style == kNeox ? launch_dec_d<64, 0>(rope, merge_ways, plan, args, st) : launch_dec_d<64, 1>(rope, merge_ways, plan, args, st);
-    return style == kNeox ? launch_dec_d<128, 0>(rope, merge_ways, plan, args, st) : launch_dec_d<128, 1>(rope, merge_ways, plan, args, st);
+        return style == kNeox ? launch_dec_d<64, 0>(rope, plan, args, st) : launch_dec_d<64, 1>(rope, plan, args, st);
+    return style == kNeox ? launch_dec_d<128, 0>(rope, plan, args, st) : launch_dec_d<128, 1>(rope, plan, args, st);
 }
 
 int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {

@@ -355,3 +355,22 @@ def test_noalloc_decode_refuses_batches_beyond_its_scratch():
     assert rc == B.PIC_EWORKSPACE
     msg = lib.pic_last_error().decode()
     assert "scratch" in msg and str(need) in msg
+
+
+def test_noalloc_decode_accepts_batches_that_just_fit_its_scratch():
+    # 504 partial slots leave 16 KB of the 64 MiB for the group table and block maps of 121
+    # requests: with one merge block per query head instead of one per eight they would not
+    # fit.  The call gets past the scratch check, and fails at its first HIP call or, with a
+    # GPU, on the misaligned q: nothing is launched either way.
+    lib = B.lib()
+    lens = [529] * 118 + [5808, 12144, 10560]
+    cfg = P.make_config(64, 4, 128)
+    hb = B.HostBatch(lens, np.arange(122), np.zeros(121), np.full(121, W.PDEP))
+    shape = P.pic_plan_shape(cfg, hb, True)
+    assert shape["partial_slots"] == 504 and shape["upload_launches"] == 2
+    # eight query heads per merge block, but one for the requests of more than eight splits
+    assert shape["merge_blocks"] <= 118 * 8 + 3 * 64
+    dev = B.pic_batch_dev(16, 1000, 16)
+    rc = lib.pic_attn_decode_noalloc(ctypes.byref(cfg), ctypes.byref(hb.c), ctypes.byref(dev), None, 8, 16, 16, 16, 16,
+                                     None)
+    assert rc in (B.PIC_EHIP, B.PIC_EINVAL), lib.pic_last_error().decode()

@@ -30,6 +30,8 @@ def _gpu():
     (32, 8, 128, [4095]),          # 256 blocks: 64 splits
     (28, 4, 128, [4096, 40]),      # 257 blocks: 65 splits, thirty-two thread rows
     (12, 12, 64, [6000]),          # 94 splits of heads that fill two workgroups
+    (28, 4, 128, [9000, 700, 150, 40]),   # thirty-two, eight and one thread row in one launch
+    (40, 8, 64, [900, 200]),       # eight and one, the last block of one half empty
 ])
 def test_decode_split_and_merge_edges(Hq, Hkv, D, lens):
     # the partials and their sums are float32 in every form: the tolerance of any bf16 decode
@@ -46,3 +48,23 @@ def test_decode_split_and_merge_edges(Hq, Hkv, D, lens):
         db.attend()
         torch.cuda.synchronize()
         assert_close(to_np(db.o), ref, wl.dtype, wl.name + " without workspace")
+
+
+def test_decode_merge_without_room_for_its_map():
+    # 66 requests: their merge map travels through the workspace.  One that ends before the
+    # wider merge's entries is accepted, with one thread row per query head
+    from paper_2606_13126_amd import _binding as B
+    lens = [70] * 65 + [3200]
+    wl = W.build("decode_merge_map", [[Sp(n, S), Sp(1, Pd, fresh=True)] for n in lens], num_q_heads=32, num_kv_heads=8,
+                 head_dim=64, rope_theta=5e5, dtype=torch.bfloat16, seed=94, value_scale=0.5,
+                 num_blocks=sum(lens) // 16 + 3 * len(lens) + 16, decode=True)
+    db = gpu_run(wl)
+    shape = B.pic_plan_shape(db.cfg, db.host, True)
+    assert shape["upload_launches"] == 1 and shape["merge_blocks"] == 65 * 4 + 32
+    ref = WO.run(wl)
+    assert_close(to_np(db.o), ref, wl.dtype, wl.name)
+    db.workspace = db.workspace[:-64]
+    db.o.fill_(float("nan"))
+    db.attend()
+    torch.cuda.synchronize()
+    assert_close(to_np(db.o), ref, wl.dtype, wl.name + " one row per head")
