@@ -207,7 +207,7 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
         int64_t max_rows = 0, token_heads = 0;
         for (auto& g : hp.groups) {
             max_rows = std::max<int64_t>(max_rows, (int64_t)g.n_tok * G);
-            token_heads += (int64_t)g.n_tok * c->num_q_heads;
+            token_heads += ((int64_t)g.n_tok * c->num_q_heads + 7) / 8 * 8;
         }
         if (token_heads > (1 << 22))
             return fail(PIC_EINVAL, "batch too large for one call (split it into several calls)");

@@ -336,6 +336,16 @@ def test_decode_256_requests_is_one_launch_filling_the_chip():
     assert shape["upload_launches"] == 4
 
 
+@pytest.mark.parametrize("n,status", [(262144, B.PIC_OK), (262145, B.PIC_EINVAL)])
+def test_float32_batches_are_limited_by_their_token_heads(n, status):
+    # 2^22 (token, query head) pairs per call, each span's counted in eights: 9 tokens of one
+    # head are 16
+    hb = B.HostBatch(np.full(n, 9), np.arange(n + 1), np.zeros(n), np.full(n, W.SSEP | W.QUERY))
+    cfg = P.make_config(1, 1, 64, dtype=B.PIC_F32)
+    size = ctypes.c_size_t()
+    assert B.lib().pic_workspace_size(ctypes.byref(cfg), ctypes.byref(hb.c), 0, ctypes.byref(size)) == status
+
+
 def test_noalloc_decode_refuses_batches_beyond_its_scratch():
     # 255 requests of 4097 keys: 2 key splits each (510 partial slots), more than the
     # no-allocation entry point's 64 MiB of scratch.  Refused on the host with
