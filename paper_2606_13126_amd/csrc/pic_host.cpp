@@ -227,8 +227,10 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
                                                        : (int64_t)INT32_MAX;
         for (auto& g : hp.groups) {
             const int64_t tiles = ((int64_t)g.tok0 + g.n_tok - g.win + tk - 1) / tk;
-            g.n_split = (int32_t)((tiles + chunk - 1) / chunk);
-            g.split_keys = (int32_t)((tiles + g.n_split - 1) / g.n_split * tk);
+            const int64_t n_split = (tiles + chunk - 1) / chunk, each = (tiles + n_split - 1) / n_split;
+            // no split past the end: its first key would overflow near 2^31 keys
+            g.n_split = (int32_t)((tiles + each - 1) / each);
+            g.split_keys = (int32_t)std::min<int64_t>(each * tk, INT32_MAX);
         }
         std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
             return std::min(x.split_keys, x.tok0 + x.n_tok - x.win) > std::min(y.split_keys, y.tok0 + y.n_tok - y.win);
@@ -779,7 +781,7 @@ pic_status pic_plan_debug(const pic_config* cfg, const pic_batch_host* batch, in
                         const int32_t rh = std::min(rl + hp.tile_rows(), g.n_tok * G);
                         const int32_t t_last = g.tok0 + (rh - 1) / G;
                         const int32_t kl = g.win + s * g.split_keys;
-                        const int32_t kh = std::min(kl + g.split_keys, t_last + 1);
+                        const int32_t kh = (int32_t)std::min<int64_t>((int64_t)kl + g.split_keys, t_last + 1);
                         if (kl >= kh) continue;
                         const int32_t slot =
                             g.n_split > 1 ? g.part_base + (kvh * g.n_split + s) * n_rt + rt : -1;

@@ -2209,7 +2209,8 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     const int row_hi = min(row_lo + NW * 16, g.n_tok * G);
     const int t_last = g.tok0 + (row_hi - 1) / G;
     const int kv_lo = g.win + ic.split * g.split_keys;
-    const int kv_hi = g.n_split > 1 ? min(kv_lo + g.split_keys, t_last + 1) : t_last + 1;
+    // (no sum below passes the last key: a request may have 2^31 - 1 of them)
+    const int kv_hi = g.split_keys < t_last + 1 - kv_lo ? kv_lo + g.split_keys : t_last + 1;
     if (kv_lo >= kv_hi) return;
     if (tid == 0) vbad = 0;
 
@@ -2286,7 +2287,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     const float* kpool = static_cast<const float*>(a.k_pool);
     const float* vpool = static_cast<const float*>(a.v_pool);
     const int sk = tid / TPK, sub = tid % TPK;
-    const int n_tiles = (kv_hi - kv_lo + TK - 1) / TK;
+    const int n_tiles = (kv_hi - kv_lo - 1) / TK + 1;
     int k_el[KU][2];
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
@@ -2297,7 +2298,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
     int32_t m_blk = 0, m_pos = 0, m_row = 0;   // block, position and row within the block of the staged key
     auto load_meta = [&](int t) {
         // a key past the range stands for its last key (its score is masked)
-        const int j = min(kv_lo + t * TK + sk, kv_hi - 1);
+        const int j = kv_lo + min(t * TK + sk, kv_hi - 1 - kv_lo);
         m_blk = btab[j >> 4];
         m_row = j & 15;
         if (ROPE) m_pos = a.positions[g.pos_off + j];
@@ -2407,13 +2408,13 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
             f32x4v_t s[KB];
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) s[kb] = tree[kb][LV];
-            const bool masked = kt + TK > kv_hi || kt + TK - 1 > wave_tmin;
+            const bool masked = kv_hi - kt < TK || wave_tmin - kt < TK - 1;
             if (masked) {
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        if (kt + 16 * kb + 4 * q4 + r > hi_key) s[kb][r] = -INFINITY;
+                        if (16 * kb + 4 * q4 + r > hi_key - kt) s[kb][r] = -INFINITY;
             }
             float mx = kNegBig;
 #pragma unroll
@@ -2446,7 +2447,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
                         for (int kq = 0; kq < 4; ++kq) {
                             const int key = 16 * kb + 4 * kq + r;
                             const float p = __shfl(s[kb][r], 16 * kq + c16);
-                            if (kt + key <= hi_key) {
+                            if (key <= hi_key - kt) {
 #pragma unroll
                                 for (int db = 0; db < DB; ++db)
 #pragma unroll

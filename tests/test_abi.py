@@ -336,6 +336,18 @@ def test_decode_256_requests_is_one_launch_filling_the_chip():
     assert shape["upload_launches"] == 4
 
 
+@pytest.mark.parametrize("is_decode", [False, True])
+@pytest.mark.parametrize("win", [0, 5])
+def test_float32_splits_cover_the_longest_request(is_decode, win):
+    # 2^31 - 1 keys: a split's end must not overflow, nor a split start past the last key
+    L = 2 ** 31 - 1
+    hb = B.HostBatch([L], [0, 2], [0, L - 1], [W.SSEP, W.PDEP | W.QUERY], [0, win])
+    items = P.pic_plan_debug(P.make_config(1, 1, 64, dtype=B.PIC_F32), hb, is_decode)
+    ranges = sorted((int(it[4]), int(it[5])) for it in items)
+    assert len(ranges) > 1 and ranges[0][0] == win and ranges[-1][1] == L
+    assert all(a[1] == b[0] for a, b in zip(ranges, ranges[1:]))
+
+
 @pytest.mark.parametrize("n,status", [(262144, B.PIC_OK), (262145, B.PIC_EINVAL)])
 def test_float32_batches_are_limited_by_their_token_heads(n, status):
     # 2^22 (token, query head) pairs per call, each span's counted in eights: 9 tokens of one
