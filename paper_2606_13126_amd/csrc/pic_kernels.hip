@@ -2262,18 +2262,24 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_f32(const Plan plan, const Ar
                     }
                 }
             } else {
-                // pairs 8 c + 2 q4 and the next: half of the four entries that start at an even quad
+                // pairs 8 c + 2 q4 and the next
 #pragma unroll
                 for (int c = 0; c < KC; ++c) {
-                    float cc[4], ss[4];
-                    cs4(pos, (8 * c + 2 * q4) & ~3, cc, ss);
-                    const int o = (q4 & 1) * 2;
+                    const int i = 8 * c + 2 * q4;
+                    f32x4v_t cs;   // cos, sin of either
+                    if (TABLE && (uint32_t)pos < (uint32_t)a.rope_len) {
+                        cs = *reinterpret_cast<const f32x4v_t*>(reinterpret_cast<const float2*>(a.rope_table) + (size_t)pos * HALF + i);
+                    } else {
+                        float c0, s0, c1, s1;
+                        rope_cs(pos, a.fstep[i], c0, s0);
+                        rope_cs(pos, a.fstep[i + 1], c1, s1);
+                        cs = f32x4v_t{c0, s0, c1, s1};
+                    }
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
-                        const float ce = o ? cc[2 + m] : cc[m], se = o ? ss[2 + m] : ss[m];
                         const float x = q[c][2 * m], y = q[c][2 * m + 1];
-                        q[c][2 * m] = x * ce - y * se;
-                        q[c][2 * m + 1] = y * ce + x * se;
+                        q[c][2 * m] = x * cs[2 * m] - y * cs[2 * m + 1];
+                        q[c][2 * m + 1] = y * cs[2 * m] + x * cs[2 * m + 1];
                     }
                 }
             }
