@@ -121,6 +121,7 @@ struct HostPlan {
     bool dec_kernel = false;   // decode through the one-query kernel (bf16, G <= kDecMaxG)
     int merge_ways = 1;        // most thread rows that share a query head's splits in the decode merge
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
+    bool short_items = false;  // prefill of rotated keys: without the alternating kernel
     pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
 };
@@ -131,6 +132,30 @@ int32_t round_up(int64_t x, int64_t m) { return (int32_t)((x + m - 1) / m * m); 
 int64_t dec_head_groups(const pic_config* c) {
     const int64_t per_wg = pic::dec_kv_per_wg(c->head_dim, c->num_kv_heads, c->num_q_heads / c->num_kv_heads);
     return (c->num_kv_heads + per_wg - 1) / per_wg;
+}
+
+// Whether a prefill over rotated keys has items too short for the alternating kernel
+// (prefill_direct): filling and draining its phases costs an item 0.6-0.85 us against
+// prefill_bf16 without rotation, and a tile gains 0.1-0.15 us where both halves of the
+// waves have rows (more than 128).  prefill_bf16 against prefill_direct at D = 128:
+// 60 x (2 x 90 + 20) tokens (2.2 tiles per item) 115.6 against 124.4 us; 8 x 6 x 400 (4.8)
+// 173 against 179; 8 x 6 x 500 (6.0) 237 against 237; 32 x 64 queries over 512 keys (9)
+// 29.1 against 28.7, but 33.6 against 34.2 for 12 heads without groups (64 rows).  At D = 64
+// the line lies higher: 8 x 4 x 700 (7.6) 162.2 against 162.4, 64 over 512 keys (9) 19.8
+// against 19.3.
+bool short_items(const pic_config* c, const HostPlan& hp) {
+    const int G = c->num_q_heads / c->num_kv_heads;
+    int64_t items = 0, tiles = 0;   // items that see a key; tiles of those with more than 128 rows
+    for (const auto& g : hp.groups) {
+        const int64_t rows = (int64_t)g.n_tok * G;
+        for (int64_t lo = 0; lo < rows; lo += pic::kTileRows) {
+            const int64_t hi = std::min<int64_t>(lo + pic::kTileRows, rows);
+            const int64_t keys = (int64_t)g.tok0 + (hi - 1) / G + 1 - g.win;
+            items += (keys + g.split_keys - 1) / g.split_keys;
+            if (hi - lo > pic::kTileRows / 2) tiles += (keys + pic::kTileKeys - 1) / pic::kTileKeys;
+        }
+    }
+    return tiles < items * (c->head_dim == 128 ? 5 : 8);
 }
 
 // Groups, their split policy and bases.  Prefill and float32 groups hold (row tile,
@@ -259,6 +284,7 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
             g.n_split = (int32_t)((tiles + cap - 1) / cap);
             g.split_keys = (int32_t)(((tiles + g.n_split - 1) / g.n_split) * pic::kTileKeys);
         }
+        if (c->k_prerotated) hp.short_items = short_items(c, hp);
         // heaviest items first
         std::stable_sort(hp.groups.begin(), hp.groups.end(), [](const pic::Group& x, const pic::Group& y) {
             const int64_t cx = (int64_t)std::min(x.n_tok, pic::kTileRows) * std::min<int64_t>(x.split_keys, x.tok0 + x.n_tok - x.win);
@@ -562,7 +588,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
         return st;
     const bool rope_on = c->k_prerotated == 0;
     const int e = hp.dec_kernel ? pic::launch_decode(c->rope_style, c->head_dim, rope_on, p, a, stream)
-                                : pic::launch_attention(c->dtype, hp.f32_waves, c->rope_style, c->head_dim, rope_on, p, a, stream);
+                                : pic::launch_attention(c->dtype, hp.f32_waves, hp.short_items, c->rope_style, c->head_dim, rope_on, p, a, stream);
     return hip_status(e, "attention launch");
 }
 

@@ -194,7 +194,7 @@ int launch_blocks_copy(int dtype, int hkv, int d, void* k_pool, void* v_pool, vo
                        const int32_t* block_ids, int n, bool to_pool, void* stream);
 int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x,
                        int n, int heads, const int32_t* positions, void* stream);
-int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
+int launch_attention(int dtype, int f32_waves, bool short_items, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& args, void* stream);
 int launch_rope_keys(int style, int d, const KeyPlan& plan, const Args& args, void* stream);
 int launch_plan_upload(const PlanUpload& up, void* stream);

@@ -660,7 +660,8 @@ __global__ void __launch_bounds__(256) rope_keys(const KeyPlan plan, const Args 
 // group); wave w owns rows [32w, 32w+32) as the 32 columns of its MFMA tiles.
 // Per 64-key tile (double-buffered in LDS, the next tile's global loads in flight
 // while the current one is consumed):
-//   ks[64][D]  rotated K, bf16, 16-byte chunks XOR-swizzled by key;
+//   ks[64][D]  rotated K, bf16, 16-byte chunks XOR-swizzled by key (ROPE: rotated on its
+//              way; otherwise as stored, the pre-rotated path's short items);
 //   vs[64][D]  V as stored (bf16), same swizzle.
 //   S^T (64 keys x 32 queries) = K Q^T: A = K from LDS, B = Q in registers, as two
 //   32-key halves whose MFMA chains interleave.  After the MFMA lane l holds query
@@ -670,7 +671,7 @@ __global__ void __launch_bounds__(256) rope_keys(const KeyPlan plan, const Args 
 //   for 16-key steps; the matching A operand (32 dims x the same 8 keys per lane)
 //   comes straight from the untransposed V tile through ds_read_b64_tr_b16.
 // ---------------------------------------------------------------------------------
-template <int D, int STYLE, bool TABLE>
+template <int D, int STYLE, bool ROPE, bool TABLE>
 __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const Plan plan, const Args a) {
     constexpr int KD = D / 16;    // 16-wide contraction steps of QK^T
     constexpr int DB = D / 32;    // 32-row blocks of O^T
@@ -709,7 +710,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     // phase steps of the in-kernel cos/sin: staged in LDS when every position needs
     // them (no table); with a table only positions outside it read them, from the
     // kernel arguments
-    if (!TABLE) {
+    if (ROPE && !TABLE) {
         for (int i = tid; i < HALF; i += kThreads) fstep[i] = a.fstep[i];
     }
     const uint64_t* fsteps = TABLE ? a.fstep : fstep;
@@ -732,7 +733,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
 #pragma unroll
         for (int kd = 0; kd < KD; ++kd)   // KD loads on every lane (a row past the tile reads the group's first)
             qraw[kd] = *reinterpret_cast<const u32x4_t*>(qp + model_chunk(a.chunk_map, 2 * kd + hi) * 8);
-        if (row_valid) qpos = a.positions[g.pos_off + g.tok0 + toff];
+        if (ROPE && row_valid) qpos = a.positions[g.pos_off + g.tok0 + toff];
     };
     auto q_finish = [&]() {   // rotate, scale by softmax_scale*log2(e), round to bf16
         float xf[KD][8];
@@ -744,7 +745,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
                 xf[kd][2 * m] = bf_lo(w);
                 xf[kd][2 * m + 1] = bf_hi(w);
             }
-        {
+        if (ROPE) {
             const int32_t pos = qpos;
             if (STYLE == kNeox) {
 #pragma unroll
@@ -797,14 +798,14 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     const uint16_t* kpool = static_cast<const uint16_t*>(a.k_pool);
     const uint16_t* vpool = static_cast<const uint16_t*>(a.v_pool);
 
-    // staging role of this thread (K, through registers): keys
+    // staging role of this thread (K through registers when it is rotated): keys
     // kk + u * (kThreads / TPK), u < SU, of every tile, 16-element slice sc
-    const bool stager = tid < NSTAGE;
+    const bool stager = ROPE && tid < NSTAGE;
     const int kk = tid / TPK, sc = tid - (tid / TPK) * TPK;
     constexpr int KSTEP = kThreads / TPK;
     const int kt0 = kv_lo & ~(kBlock - 1);
     const int n_tiles = (kv_hi - kt0 + BN - 1) / BN;
-    // direct global->LDS role (V): lane `lane` of wave
+    // direct global->LDS role (V always, K too without RoPE): lane `lane` of wave
     // `wave` fills 16-byte chunk p = (DPW*wave + i)*64 + lane of the tile, i.e. row
     // p / CH, physical chunk p % CH, which holds logical chunk (p % CH) ^ swz(row)
     constexpr int DPW = BN * CH / (64 * kWaves);
@@ -827,7 +828,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     auto dma_meta = [&](int t) {
         if (t >= n_tiles) return;
         const int kt = kt0 + t * BN;
-        if (wave_u == 0) {
+        if (ROPE && wave_u == 0) {
             dma_lds4(a.positions + g.pos_off + clamp_key(kt, kt + lane), &mpos[t & 1][0]);
         } else if (wave_u == 1 && lane < BN / kBlock) {
             const int blk = min((kt >> 4) + lane, (kv_hi - 1) >> 4);
@@ -863,6 +864,7 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
         for (int i = 0; i < DPW; ++i) {
             const int lds_off = (DPW * wave_u + i) * 64 * 8;
             dma_lds16(vpool + row_off[i], &vs[buf][lds_off]);
+            if (!ROPE) dma_lds16(kpool + row_off[i], &ks[buf][lds_off]);
         }
     };
     auto load_meta = [&](int t, TileRegs* rr) {
@@ -1023,7 +1025,6 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
         // direct loads of the next tile (no registers) go out first; the rotated-K
         // register loads wait until the score tile is dead (after the softmax)
         if (more) load_meta(t + 1, regs);
-        
         dma_meta(t + 2);   // into the slot tile t's metadata has left
         if (more) issue_direct(t + 1, buf ^ 1);
         if (wave_live) {
@@ -1183,7 +1184,8 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
 // prefill_direct
 //
 // The prefill over keys that need no rotation on their way: a pool of rotated keys
-// (k_prerotated), or the call's own rotated copy (RK, rope_keys).  Rows, tiles, operand
+// (k_prerotated, unless its items are short), or the call's own rotated copy (RK,
+// rope_keys).  Rows, tiles, operand
 // layouts and arithmetic are those of prefill_bf16; K and V both go straight to LDS.
 //
 // A wave alternates a product phase (scores of tile t, then P V of tile t - 1: matrix
@@ -2562,7 +2564,7 @@ hipError_t launch_f32_t(const Plan& plan, const Args& a, hipStream_t st) {
 }
 
 template <int D, int STYLE, bool ROPE, bool TABLE>
-hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_attn_t(int dtype, int f32_waves, bool short_items, const Plan& plan, const Args& a, hipStream_t st) {
     if (dtype == 1)
         return f32_waves == 1 ? launch_f32_t<D, STYLE, ROPE, TABLE, 1>(plan, a, st)
                               : launch_f32_t<D, STYLE, ROPE, TABLE, kF32Waves>(plan, a, st);
@@ -2570,9 +2572,11 @@ hipError_t launch_attn_t(int dtype, int f32_waves, const Plan& plan, const Args&
         if (a.k_rot != nullptr)
             hipLaunchKernelGGL((prefill_direct<D, STYLE, true, TABLE, true>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
         else
-            hipLaunchKernelGGL((prefill_bf16<D, STYLE, TABLE>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+            hipLaunchKernelGGL((prefill_bf16<D, STYLE, true, TABLE>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+    } else if (short_items) {   // (without rotation the pairing makes no difference)
+        hipLaunchKernelGGL((prefill_bf16<D, 0, false, false>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
     } else {
-        hipLaunchKernelGGL((prefill_direct<D, STYLE, false, false, false>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
+        hipLaunchKernelGGL((prefill_direct<D, 0, false, false, false>), dim3(plan.n_items), dim3(kThreads), 0, st, plan, a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2623,11 +2627,11 @@ hipError_t launch_dec_d(bool rope, const Plan& plan, const Args& a, hipStream_t 
 }
 
 template <int D, int STYLE>
-hipError_t launch_attn_d(int dtype, int f32_waves, bool rope, const Plan& plan, const Args& a, hipStream_t st) {
+hipError_t launch_attn_d(int dtype, int f32_waves, bool short_items, bool rope, const Plan& plan, const Args& a, hipStream_t st) {
     const bool table = a.rope_table != nullptr && a.rope_len > 0;
-    if (!rope) return launch_attn_t<D, STYLE, false, false>(dtype, f32_waves, plan, a, st);
-    return table ? launch_attn_t<D, STYLE, true, true>(dtype, f32_waves, plan, a, st)
-                 : launch_attn_t<D, STYLE, true, false>(dtype, f32_waves, plan, a, st);
+    if (!rope) return launch_attn_t<D, STYLE, false, false>(dtype, f32_waves, short_items, plan, a, st);
+    return table ? launch_attn_t<D, STYLE, true, true>(dtype, f32_waves, short_items, plan, a, st)
+                 : launch_attn_t<D, STYLE, true, false>(dtype, f32_waves, short_items, plan, a, st);
 }
 
 }  // namespace
@@ -2737,14 +2741,14 @@ int launch_decode(int style, int d, bool rope, const Plan& plan, const Args& arg
     return style == kNeox ? launch_dec_d<128, 0>(rope, plan, args, st) : launch_dec_d<128, 1>(rope, plan, args, st);
 }
 
-int launch_attention(int dtype, int f32_waves, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
+int launch_attention(int dtype, int f32_waves, bool short_items, int style, int d, bool rope, const Plan& plan, const Args& args, void* stream) {
     if (plan.n_items == 0) return hipSuccess;
     hipStream_t st = (hipStream_t)stream;
     if (d == 64)
-        return style == kNeox ? launch_attn_d<64, 0>(dtype, f32_waves, rope, plan, args, st)
-                              : launch_attn_d<64, 1>(dtype, f32_waves, rope, plan, args, st);
-    return style == kNeox ? launch_attn_d<128, 0>(dtype, f32_waves, rope, plan, args, st)
-                          : launch_attn_d<128, 1>(dtype, f32_waves, rope, plan, args, st);
+        return style == kNeox ? launch_attn_d<64, 0>(dtype, f32_waves, short_items, rope, plan, args, st)
+                              : launch_attn_d<64, 1>(dtype, f32_waves, short_items, rope, plan, args, st);
+    return style == kNeox ? launch_attn_d<128, 0>(dtype, f32_waves, short_items, rope, plan, args, st)
+                          : launch_attn_d<128, 1>(dtype, f32_waves, short_items, rope, plan, args, st);
 }
 
 }  // namespace pic
