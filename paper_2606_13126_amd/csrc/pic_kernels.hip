@@ -322,73 +322,78 @@ __global__ void __launch_bounds__(256) rope_table_kernel(void* __restrict__ tabl
 }
 
 // ---------------------------------------------------------------------------------
-// rope_rotate: x[row][h][:] <- R_{pos[row]} x[row][h][:], eight pairs (16 elements) per
-// thread in 16-byte accesses.  Bound by memory; one pair per thread in 2-byte accesses
-// took 12.1 us for 2,176 rows of 32 heads x 128 dims of bf16 (36 MB moved), this form
-// 6.7 us.
+// rope_rotate: x[row][h][:] <- R_{pos[row]} x[row][h][:], PP pairs (2 PP elements) per
+// thread in accesses of up to 16 bytes.  Large calls (PP = 8) are bound by memory; one pair
+// per thread in 2-byte accesses took 12.1 us for 2,176 rows of 32 heads x 128 dims of bf16
+// (36 MB moved), this form 6.7 us.  Small calls are bound by one thread's chain of loads,
+// sines and stores (launch_rope_rotate has the line).
 // ---------------------------------------------------------------------------------
-template <typename T, int STYLE>
+template <typename T, int STYLE, int PP>
 __global__ void __launch_bounds__(256) rope_rotate_kernel(T* __restrict__ x, int64_t n_units, int heads, int d,
                                                           int rot_half, RopeSteps steps,
                                                           const int32_t* __restrict__ positions,
                                                           const void* __restrict__ table, int rope_len) {
-    constexpr int V = 16 / sizeof(T);              // elements per access
+    constexpr int V = PP * sizeof(T) < 16 ? PP : 16 / sizeof(T);   // elements per access
     typedef T vec_t __attribute__((ext_vector_type(V)));
+    constexpr int TW = sizeof(T) == 4 ? 2 * PP : PP;               // 4-byte words of the PP table entries
+    constexpr int TV = TW < 4 ? TW : 4;
+    typedef uint32_t tab_t __attribute__((ext_vector_type(TV)));
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= n_units) return;
-    const int upr = d / 16, half = d / 2;          // units per row of one head: 4 or 8
+    const int half = d / 2, upr = half / PP;       // units per row of one head
     const int64_t rh = idx / upr;                  // row * heads + h
-    const int i0 = (int)(idx - rh * upr) * 8;      // first pair
+    const int i0 = (int)(idx - rh * upr) * PP;     // first pair
     if (i0 >= rot_half) return;                    // past the rotary width: unchanged
     const int32_t pos = positions[rh <= UINT32_MAX ? (uint32_t)rh / (uint32_t)heads : rh / heads];
-    // NeoX: elements i0 .. i0 + 7 of both halves (rot_half is a multiple of 8); GPT-J: 2 i0 .. 2 i0 + 15
-    T* run[2] = {x + rh * d + (STYLE == kNeox ? i0 : 2 * i0), x + rh * d + (STYLE == kNeox ? i0 + rot_half : 2 * i0 + 8)};
-    T v[16];
+    // NeoX: elements i0 .. i0 + PP - 1 of both halves (rot_half is a multiple of 8); GPT-J:
+    // 2 i0 .. 2 i0 + 2 PP - 1
+    T* run[2] = {x + rh * d + (STYLE == kNeox ? i0 : 2 * i0), x + rh * d + (STYLE == kNeox ? i0 + rot_half : 2 * i0 + PP)};
+    T v[2 * PP];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int k = 0; k < 8; k += V) {
+        for (int k = 0; k < PP; k += V) {
             const vec_t w = *reinterpret_cast<const vec_t*>(run[h] + k);
 #pragma unroll
-            for (int e = 0; e < V; ++e) v[8 * h + k + e] = w[e];
+            for (int e = 0; e < V; ++e) v[PP * h + k + e] = w[e];
         }
-    float c[8], s[8];
+    float c[PP], s[PP];
     if (table != nullptr && (uint32_t)pos < (uint32_t)rope_len) {
-        const u32x4_t* t = reinterpret_cast<const u32x4_t*>(static_cast<const char*>(table) +
-                                                            ((size_t)pos * half + i0) * (sizeof(T) == 4 ? 8 : 4));
+        const tab_t* t = reinterpret_cast<const tab_t*>(static_cast<const uint32_t*>(table) + ((size_t)pos * half + i0) * (TW / PP));
 #pragma unroll
-        for (int k = 0; k < (sizeof(T) == 4 ? 4 : 2); ++k) {
-            const u32x4_t w = t[k];
+        for (int k = 0; k < TW / TV; ++k) {
+            const tab_t w = t[k];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
+            for (int e = 0; e < TV; ++e) {
+                const int word = TV * k + e;
                 if (sizeof(T) == 4) {
-                    (e & 1 ? s : c)[2 * k + e / 2] = __uint_as_float(w[e]);
+                    (word & 1 ? s : c)[word / 2] = __uint_as_float(w[e]);
                 } else {
-                    c[4 * k + e] = bf_lo(w[e]);
-                    s[4 * k + e] = bf_hi(w[e]);
+                    c[word] = bf_lo(w[e]);
+                    s[word] = bf_hi(w[e]);
                 }
             }
         }
     } else {
 #pragma unroll
-        for (int k = 0; k < 8; ++k) rope_cs(pos, steps.s[i0 + k], c[k], s[k]);
+        for (int k = 0; k < PP; ++k) rope_cs(pos, steps.s[i0 + k], c[k], s[k]);
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < PP; ++k) {
         if (STYLE != kNeox && i0 + k >= rot_half) break;
         T& ta = v[STYLE == kNeox ? k : 2 * k];
-        T& tb = v[STYLE == kNeox ? 8 + k : 2 * k + 1];
+        T& tb = v[STYLE == kNeox ? PP + k : 2 * k + 1];
         const float a = (float)ta, b = (float)tb;
-        ta = (T)(a * c[k] - b * s[k]);
-        tb = (T)(b * c[k] + a * s[k]);
+        ta = (T)__builtin_fmaf(a, c[k], -(b * s[k]));   // named, so that every PP rounds alike
+        tb = (T)__builtin_fmaf(a, s[k], b * c[k]);
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int k = 0; k < 8; k += V) {
+        for (int k = 0; k < PP; k += V) {
             vec_t w;
 #pragma unroll
-            for (int e = 0; e < V; ++e) w[e] = v[8 * h + k + e];
+            for (int e = 0; e < V; ++e) w[e] = v[PP * h + k + e];
             *reinterpret_cast<vec_t*>(run[h] + k) = w;
         }
 }
@@ -2696,27 +2701,36 @@ int launch_rope_table(int dtype, int d, const RopeSteps& steps, int n_pos, float
     return hipGetLastError();
 }
 
+namespace {
+template <typename T, int PP>
+void rope_rotate_t(int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x, int64_t rows,
+                   int heads, const int32_t* positions, hipStream_t st) {
+    const int64_t n_units = rows * heads * (d / 2 / PP);
+    const dim3 grid((unsigned)((n_units + 255) / 256));
+    if (style == kNeox)
+        hipLaunchKernelGGL((rope_rotate_kernel<T, 0, PP>), grid, dim3(256), 0, st, static_cast<T*>(x), n_units, heads, d, rot_half,
+                           steps, positions, static_cast<const void*>(table), rope_len);
+    else
+        hipLaunchKernelGGL((rope_rotate_kernel<T, 1, PP>), grid, dim3(256), 0, st, static_cast<T*>(x), n_units, heads, d, rot_half,
+                           steps, positions, static_cast<const void*>(table), rope_len);
+}
+}  // namespace
+
 int launch_rope_rotate(int dtype, int style, int d, int rot_half, const RopeSteps& steps, const float* table, int rope_len, void* x, int n,
                        int heads, const int32_t* positions, void* stream) {
-    const int64_t n_units = (int64_t)n * heads * (d / 16);
-    if (n_units == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n_units + 255) / 256));
-    const void* t = table;
+    if (n == 0) return hipSuccess;
     hipStream_t st = (hipStream_t)stream;
+    // Two pairs per thread while eight would leave at most half a workgroup per CU, else
+    // 16-byte accesses (float32: four pairs).  Eight against two, no table: 33 rows of 8 heads
+    // x 128 of float32 3.6 against 2.5 us, 256 x 32 x 64 of bf16 3.4 against 2.7; with a table
+    // 2,048 x 32 x 128 of bf16 6.4 against 8.5, of float32 (four) 10.6 against 13.2.
+    const bool small = (int64_t)n * heads * (d / 16) <= 128 * 256;
     if (dtype == 1) {
-        if (style == kNeox)
-            hipLaunchKernelGGL((rope_rotate_kernel<float, 0>), grid, dim3(256), 0, st, static_cast<float*>(x),
-                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
-        else
-            hipLaunchKernelGGL((rope_rotate_kernel<float, 1>), grid, dim3(256), 0, st, static_cast<float*>(x),
-                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
+        if (small) rope_rotate_t<float, 2>(style, d, rot_half, steps, table, rope_len, x, n, heads, positions, st);
+        else rope_rotate_t<float, 4>(style, d, rot_half, steps, table, rope_len, x, n, heads, positions, st);
     } else {
-        if (style == kNeox)
-            hipLaunchKernelGGL((rope_rotate_kernel<__bf16, 0>), grid, dim3(256), 0, st, static_cast<__bf16*>(x),
-                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
-        else
-            hipLaunchKernelGGL((rope_rotate_kernel<__bf16, 1>), grid, dim3(256), 0, st, static_cast<__bf16*>(x),
-                               n_units, heads, d, rot_half, steps, positions, t, rope_len);
+        if (small) rope_rotate_t<__bf16, 2>(style, d, rot_half, steps, table, rope_len, x, n, heads, positions, st);
+        else rope_rotate_t<__bf16, 8>(style, d, rot_half, steps, table, rope_len, x, n, heads, positions, st);
     }
     return hipGetLastError();
 }
