@@ -396,3 +396,13 @@ def test_noalloc_decode_accepts_batches_that_just_fit_its_scratch():
     rc = lib.pic_attn_decode_noalloc(ctypes.byref(cfg), ctypes.byref(hb.c), ctypes.byref(dev), None, 8, 16, 16, 16, 16,
                                      None)
     assert rc in (B.PIC_EHIP, B.PIC_EINVAL), lib.pic_last_error().decode()
+
+
+@pytest.mark.parametrize("keys,copied", [(131072, True), (131073, False)])
+def test_key_copy_is_planned_up_to_its_limit(keys, copied):
+    # 512 queries of 64 / 8 heads x 128 over 131,072 keys: a copy of exactly 256 MiB
+    hb = B.HostBatch([keys], [0, 2], [0, keys - 512], [W.SSEP, W.PDEP | W.QUERY])
+    cfg = P.make_config(64, 8, 128, rope_theta=5e5)
+    parts = P.pic_plan_shape(cfg, hb, False)["partial_slots"] * 256 * (128 + 2) * 4
+    size = P.pic_workspace_size(cfg, hb, False)
+    assert size == parts + (256 << 20 if copied else 0)

@@ -1,6 +1,7 @@
 """GPU: the float32 kernel at the edges of its tiles (16 query rows per wave, 64 per
 workgroup, 16- and 32-key tiles, 128-key splits), with and without room for split
-partials, and with infinities that only some rows see."""
+partials, with the groups in the kernel arguments and in the workspace, and with
+infinities that only some rows see."""
 import numpy as np
 import pytest
 import torch
@@ -41,6 +42,27 @@ def test_f32_tile_edges(Hq, Hkv, D, cached, fresh, style):
     db.attend()
     torch.cuda.synchronize()
     assert_close(to_np(db.o), ref, wl.dtype, wl.name + " without workspace")
+
+
+@pytest.mark.parametrize("decode", [False, True])
+def test_f32_splits_of_many_groups(decode):
+    # 66 requests: groups and merge map travel through the workspace, beside the partials
+    from paper_2606_13126_amd import _binding as B
+    lens = [40] * 64 + [700, 1500]
+    reqs = [[Sp(n, S), Sp(1, Pd, fresh=True) if decode else Sp(3 + 20 * (n > 600), Pd | Q, fresh=True)] for n in lens]
+    wl = W.build(f"f32_many_{decode}", reqs, num_q_heads=6, num_kv_heads=2, head_dim=64, rope_theta=1e4, dtype=torch.float32,
+                 seed=98, num_blocks=sum(lens) // 16 + 4 * len(lens) + 16, decode=decode)
+    db = gpu_run(wl, rope_style=1)
+    shape = B.pic_plan_shape(db.cfg, db.host, decode)
+    assert shape["upload_launches"] == 1 and shape["merge_blocks"] > 0
+    ref = WO.run(wl, style="gptj")
+    assert_close(to_np(db.o), ref, wl.dtype, wl.name)
+    # room for the table and the attention map alone: unsplit
+    db.workspace = db.workspace[:66 * 48 + 256 + 4 * 1024]
+    db.o.fill_(float("nan"))
+    db.attend()
+    torch.cuda.synchronize()
+    assert_close(to_np(db.o), ref, wl.dtype, wl.name + " unsplit")
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("nan")])

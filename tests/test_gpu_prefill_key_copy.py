@@ -1,7 +1,8 @@
 """GPU: a prefill whose keys are seen by many row tiles rotates them once, into a copy
 in the workspace.  Windows that start and end inside cache blocks, two segments that
 share a block, positions outside the cos/sin table, both pairings and head sizes,
-partial rotary width; and the same call with a workspace that ends before the copy."""
+partial rotary width; more groups than the kernel arguments hold; the most segments a copy
+has; a captured call; and the same calls with a workspace that ends before the copy."""
 import numpy as np
 import pytest
 import torch
@@ -83,3 +84,84 @@ def test_key_copy_reads_no_key_outside_the_windows():
     db.attend()
     torch.cuda.synchronize()
     assert_close(to_np(db.o), ref, wl.dtype, "key copy with NaN outside the windows")
+
+
+def attend_both(db, wl, copy_bytes, rows=None):
+    """The outputs with the copy and with a workspace that ends just before it."""
+    out = []
+    full = db.workspace
+    for ws in (full, full[: full.numel() - copy_bytes]):
+        db.workspace = ws
+        db.o.fill_(float("nan"))
+        db.attend()
+        torch.cuda.synchronize()
+        out.append(to_np(db.o))
+    db.workspace = full
+    return out
+
+
+def test_key_copy_with_groups_in_the_workspace():
+    # 66 short fresh documents between the cached ones and the tail: 67 groups go through the
+    # workspace's table, and with them where each finds its keys in the copy
+    from paper_2606_13126_amd import _binding as B
+    from paper_2606_13126_amd.runner import DeviceBatch
+    spans = [Sp(n, S) for n in (37, 1999, 705)] + [Sp(5, S | Q, fresh=True) for _ in range(66)]
+    wl = W.small_case("key_copy_many", [spans + [Sp(208, Pd | Q, fresh=True)]], Hq=128, Hkv=8, D=128, theta=5e5,
+                      dtype=torch.bfloat16, seed=100, value_scale=0.5)
+    db = DeviceBatch(wl, table_positions=int(wl.positions.max()) + 1)
+    shape = B.pic_plan_shape(db.cfg, db.host, False)
+    assert shape["groups"] == 67 and shape["upload_launches"] == 1
+    copy = -(-int(wl.seq_lens[0]) // 16) * 8 * 16 * 128 * 2
+    before = shape["partial_slots"] * 256 * (128 + 2) * 4 + 67 * 48 + 4 * (shape["attention_blocks"] + shape["merge_blocks"])
+    assert before + copy <= db.workspace.numel() <= before + copy + 4 * 256    # the copy comes last
+    db.write()
+    ref = WO.run(wl)
+    for got, what in zip(attend_both(db, wl, copy), ("copy", "no copy")):
+        assert_close(got, ref, wl.dtype, f"{wl.name} {what}")
+
+
+@pytest.mark.parametrize("n,copied", [(64, True), (65, False)])
+def test_key_copy_segments(n, copied):
+    # documents that see themselves, apart from each other: a segment each, at most 64
+    from paper_2606_13126_amd.runner import DeviceBatch
+    spans = []
+    for _ in range(n):
+        spans += [Sp(3, S), Sp(208, S | Q, fresh=True)]
+    wl = W.small_case(f"key_copy_{n}_segments", [spans], Hq=128, Hkv=8, D=64, theta=5e5, dtype=torch.bfloat16, seed=101,
+                      value_scale=0.5)
+    db = DeviceBatch(wl, table_positions=int(wl.positions.max()) + 1)
+    at = [211 * i + 3 for i in range(n)]
+    copy = sum((a + 207) // 16 - a // 16 + 1 for a in at) * 8 * 16 * 64 * 2
+    assert (db.workspace.numel() >= copy) == copied
+    db.write()
+    rows = list(range(0, 208 * n, 499))
+    ref = WO.run(wl, rows=rows)
+    for got, what in zip(attend_both(db, wl, copy if copied else 0), ("copy", "no copy")):
+        assert np.isfinite(got).all()
+        assert_close(got[rows], ref, wl.dtype, f"{wl.name} {what}")
+
+
+def test_key_copy_captured():
+    from paper_2606_13126_amd.runner import DeviceBatch
+    wl = case(128, 208, (37, 1999, 705))
+    db = DeviceBatch(wl, table_positions=int(wl.positions.max()) + 1)
+    db.write()
+    db.attend()
+    torch.cuda.synchronize()
+    ref = db.o.clone()
+    g, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            db.write()
+            db.attend()
+    for r in range(3):
+        torch.cuda.synchronize()
+        db.o.fill_(7.0)
+        db.workspace.fill_(255)
+        junk = torch.randn(1 << 20, device="cuda").sum()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        say(f"  replay {r}: junk={float(junk):.3f}")
+        assert torch.equal(db.o.view(torch.int16), ref.view(torch.int16))

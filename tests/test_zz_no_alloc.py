@@ -64,6 +64,20 @@ def test_noalloc_decode_matches_workspace_decode_two_calls():
         torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("lens", [[1500, 90], [40] * 64 + [700, 1500]])
+def test_noalloc_decode_float32(lens):
+    # the key splits' partials live in the scratch, for more than 64 requests after the
+    # previous call's and beside the group table
+    S, Pd, Sp = W.SSEP, W.PDEP, W.Span
+    wl = W.build(f"noalloc_f32_{len(lens)}", [[Sp(n, S), Sp(1, Pd, fresh=True)] for n in lens], num_q_heads=8, num_kv_heads=2,
+                 head_dim=128, rope_theta=1e4, dtype=torch.float32, seed=99, num_blocks=sum(lens) // 16 + 4 * len(lens) + 16,
+                 decode=True)
+    say(f"[gpu] noalloc float32 decode of {len(lens)} requests")
+    db, ref = _case(wl)
+    assert torch.equal(db.o.view(torch.int32), ref.view(torch.int32))
+    assert_close(to_np(db.o), WO.run(wl), wl.dtype, f"{wl.name} vs oracle")
+
+
 def test_noalloc_decode_narrow_workgroups():
     # models with one or two KV heads decode with 2- and 4-wave workgroups (three or
     # two per CU, more key splits): the scratch holds their partials too
