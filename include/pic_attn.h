@@ -186,8 +186,14 @@ pic_status pic_blocks_scatter(const pic_config* cfg, void* k_pool, void* v_pool,
  * work-group table that the call writes there before its attention launch; for a
  * prefill whose keys are shared by many query rows also room for a rotated copy of
  * those keys (at most 256 MiB).  The copy, and the partial results of float32 calls,
- * are optional: a workspace without room for them is accepted, and the call is slower.
- * May be 0.  Returned through *bytes (the status reports argument errors). */
+ * are optional, and so are the map entries of the wider split merges of a large decode
+ * batch: a workspace without room for them is accepted, and the call is slower (its
+ * results then agree within rounding, not bit for bit).  May be 0.  Returned through
+ * *bytes (the status reports argument errors).
+ *
+ * A workspace belongs to one call until that call's kernels have run: a call may write
+ * anywhere in the bytes it is given, so calls that can overlap (on several streams, from
+ * several threads) need a workspace each, whatever their type and size. */
 pic_status pic_workspace_size(const pic_config* cfg, const pic_batch_host* batch, int32_t is_decode,
                               size_t* bytes);
 
@@ -217,14 +223,16 @@ pic_status pic_attn_decode(const pic_config* cfg, const pic_batch_host* batch, c
 
 /* pic_attn_decode for callers that cannot allocate device memory (code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * arguments minus the workspace, the same kernels and results.  The split-KV
- * partials and the group table live in a 64 MiB device scratch array inside the
- * library, one per GPU the library runs on, held until the process ends; the call
- * allocates nothing.  A batch needing more scratch than that is refused with
- * PIC_EWORKSPACE before anything is launched (pic_workspace_size(cfg, batch, 1)
- * gives the need).  Every call on one GPU shares that GPU's scratch: calls that
- * overlap on one GPU (concurrent streams, or from several threads) race and must
- * be serialised by the caller.  The stream must belong to the current device. */
+ * arguments minus the workspace, and the kernels and results of pic_attn_decode with a
+ * 64 MiB workspace.  The split-KV partials and the group table live in a 64 MiB device
+ * scratch array inside the library, one per GPU the library runs on, held until the
+ * process ends; the call allocates nothing.  What pic_workspace_size calls optional is
+ * left out where it does not fit; a batch that needs more scratch even so is refused with
+ * PIC_EWORKSPACE before anything is launched (pic_workspace_size(cfg, batch, 1) <= 64 MiB
+ * is enough, but not always necessary).  Every call on one GPU, of either dtype, shares
+ * that GPU's scratch: calls that overlap on one GPU (concurrent streams, or from several
+ * threads) race and must be serialised by the caller.  The stream must belong to the
+ * current device. */
 pic_status pic_attn_decode_noalloc(const pic_config* cfg, const pic_batch_host* batch, const pic_batch_dev* dev,
                                    const pic_rope_table* rope, const void* q, void* o, const void* k_pool,
                                    const void* v_pool, int32_t num_blocks, void* stream);

@@ -123,6 +123,7 @@ struct HostPlan {
     int f32_waves = 0;         // waves per workgroup of the float32 kernel (float32 only)
     bool short_items = false;  // prefill of rotated keys: without the alternating kernel
     pic::KeyPlan keys{};       // the rotated key copy (n = 0: keys are rotated in the attention kernel)
+    bool keys_from_table = true;   // whether the copy also pays where a cos/sin table makes rotation cheap
     int tile_rows() const { return f32_waves ? 16 * f32_waves : pic::kTileRows; }
 };
 
@@ -376,7 +377,17 @@ WsLayout ws_layout(const pic_config* c, const HostPlan& hp) {
 // rotating in the attention kernel against copy + attention: one 33,280-token prompt
 // (20 row tiles per key) 903 against 784 us; 16 tails of 128 tokens over 4,096 keys (2
 // per key) 161 against 167 us; a 256-query tail over 5,376 keys (4 per key) 41 against
-// 50 us.
+// 50 us (the 10 us hold one item per CU).  prefill_direct adds about 1.1 us to every further
+// item of a CU (filling and draining its phases): 4,440 items that see 177 keys on average took 286 us
+// rotating in the kernel, 314 us with the copy; 2,240 that see 880, 388 against 328.  This
+// holds at head_dim 128 with a cos/sin table.  At head_dim 64, where both costs halve, every
+// call past the line gains all the same (13 requests, 1,096 items: 116 against 90 us; 16 x 128
+// queries over 5,120 keys 135 against 129), and without a table rotation in the kernel costs
+// far more (1,568 items: 222 against 170 us): there the items are not counted, and as the
+// table is known only to the call, it decides on them (keys_from_table).
+// Calls of more than kMaxGroups segments or kMaxKeyCopy bytes rotate in the attention
+// kernel: where a copy of them would pay has not been measured (512 queries of 64 / 8 heads
+// over 131,072 keys, the most: 2,271 against 1,853 us).
 void plan_keys(const pic_config* c, HostPlan& hp) {
     hp.keys.n = 0;
     if (c->dtype != PIC_BF16 || c->k_prerotated || hp.dec_kernel) return;
@@ -386,7 +397,9 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
     };
     std::vector<Run> runs;
     double staged = 0.0;   // keys times the row tiles that see them
+    double items = 0.0;
     for (const auto& g : hp.groups) {
+        items += (double)pic::row_tiles(g, G, pic::kTileRows) * g.n_split * c->num_kv_heads;
         runs.push_back(Run{g.req, g.win, g.tok0 + g.n_tok, g.pos_off});
         for (int rt = 0; rt < pic::row_tiles(g, G, pic::kTileRows); ++rt)
             staged += (double)(g.tok0 + (std::min((int64_t)(rt + 1) * pic::kTileRows, (int64_t)g.n_tok * G) - 1) / G + 1 - g.win);
@@ -405,6 +418,7 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
     }
     const double gain_us = c->num_kv_heads * (0.043e-3 * staged - 0.07e-3 * (double)keys) - 10.0;
     if (gain_us <= 0 || segs.size() > (size_t)pic::kMaxGroups || key_copy_bytes(c, blocks) > pic::kMaxKeyCopy) return;
+    hp.keys_from_table = c->head_dim != 128 || gain_us > 1.1 * (items / pic::kTargetCUs - 1.0);
     hp.keys.n = (int32_t)segs.size();
     int32_t blk = 0;
     for (size_t i = 0; i < segs.size(); ++i) {
@@ -539,7 +553,7 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     a.rope_len = table ? rope->len : 0;
     char* wsb = static_cast<char*>(ws);
     a.part_o = hp.n_parts ? reinterpret_cast<float*>(wsb) : nullptr;
-    const bool copy_keys = hp.keys.n > 0 && ws != nullptr && ws_bytes >= wl.total;
+    const bool copy_keys = hp.keys.n > 0 && ws != nullptr && ws_bytes >= wl.total && (hp.keys_from_table || !table);
     a.k_rot = copy_keys ? wsb + wl.keys : nullptr;
     a.part_ml = hp.n_parts ? reinterpret_cast<float*>(wsb + wl.ml) : nullptr;
     const double scale = c->softmax_scale > 0.f ? (double)c->softmax_scale : 1.0 / std::sqrt((double)c->head_dim);

@@ -122,7 +122,7 @@ struct KeyPlan {
     int32_t n_blocks;    // blocks of the copy
     KeySegment seg[kMaxGroups];
 };
-constexpr size_t kMaxKeyCopy = (size_t)256 << 20;   // bytes of the copy: what the Infinity Cache holds
+constexpr size_t kMaxKeyCopy = (size_t)256 << 20;   // bytes of the copy: what a call may add to its workspace
 
 // Arguments of one plan-upload launch: groups [first, first + n) of the call, and
 // where the block ranges of the chunk's last group end.

@@ -132,10 +132,8 @@ __device__ __forceinline__ Words4 rot4_gptj(uint32_t w0, uint32_t w1, uint32_t w
 
 // Two rotate-half pairs (elements 2m and 2m+1 of both halves) in plain float32
 // arithmetic, for a kernel that is bound by memory and leaves the schedule to the
-// compiler.  (A dot product occupies the matrix pipe: 64 of them beside 16 MFMAs of
-// another wave of the SIMD take 375 ns, either alone 138 and 248, where 64 FMAs add
-// nothing.  The attention kernels still rotate by dot products: 8 FMA-form vector
-// instructions more per pair cost prefill_bf16 2% on 16 tails over 4,096 keys.)
+// compiler.  (The attention kernels rotate by dot products: the FMA form has 8 vector
+// instructions more per pair and cost prefill_bf16 2% on 16 tails over 4,096 keys.)
 __device__ __forceinline__ void rot2_fma(uint32_t& A, uint32_t& B, uint32_t e0, uint32_t e1) {
     const float x0 = bf_lo(A), x1 = bf_hi(A), y0 = bf_lo(B), y1 = bf_hi(B);
     const float c0 = bf_lo(e0), s0 = bf_hi(e0), c1 = bf_lo(e1), s1 = bf_hi(e1);
@@ -1199,10 +1197,11 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
 // wave in either phase.  Four slots of K and of V (128 KB at D = 128) keep the copies
 // three phases ahead.
 //
-// Bound by power: with random operands the chip holds 16 of these products and their
-// LDS reads on every SIMD at 0.65 us where zero operands take 0.45, so 64 keys x 256
-// rows cannot take less than 1.3 us; 1.65-1.8 us here (a tail of 512 x 64 queries over
-// 33,280 rotated keys: 432-460 us, 477-505 us with both waves of a SIMD in step).
+// Bound by the two units of a SIMD taking turns: on a prompt of 33,280 tokens (64 / 8 heads)
+// the matrix cores are busy 46% of its cycles, the vector unit 43%, both at once 17%
+// (prefill_bf16: 34, 44 and 9%).  64 keys x 256 rows are 64 products of 32 cycles per SIMD,
+// 0.85 us at 2.4 GHz, and take 1.65-1.8 us (a tail of 512 x 64 queries over 33,280 rotated
+// keys: 432-460 us, 477-505 us with both waves of a SIMD in step).
 // ---------------------------------------------------------------------------------
 template <int D, int STYLE, bool ROPE, bool TABLE, bool RK>
 __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_direct(const Plan plan, const Args a) {
@@ -2180,9 +2179,11 @@ __global__ void __launch_bounds__(ROWS * D / 4) decode_merge(const Plan plan, co
 //                                          so probabilities never leave their lanes
 // Row i of output block db is dimension 64 (db / 4) + 4 i + db % 4, so that one 16-byte
 // read of a V row serves four blocks and the output leaves in 16-byte stores.
-// Bound by the matrix cores: 8 D flops per (row, key) at 64 flops per cycle and SIMD;
-// one wave per (token, head) with a shuffle sum per key took 638 us on 573 queries of
-// 8 heads over up to 1,400 keys (1 TFLOP/s), this form takes 25.5 us (24 TFLOP/s).
+// 4 D flops per (row, key).  Bound by the sequence within a tile: one LDS buffer and two
+// barriers per tile put staging, scores, softmax and outputs one after another.  One
+// wave per (token, head) with a shuffle sum per key took 638 us on 573 queries of
+// 8 heads over up to 1,400 keys (1 TFLOP/s), this form takes 25.5 us (24 TFLOP/s, where
+// a library product reaches 153).
 // ---------------------------------------------------------------------------------
 typedef float f32x4v_t __attribute__((ext_vector_type(4)));
 

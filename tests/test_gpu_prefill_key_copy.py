@@ -23,6 +23,14 @@ def _gpu():
     import paper_2606_13126_amd  # noqa: F401  (fails loudly if the library is missing)
 
 
+def was_copied(db, copy_bytes):
+    """Whether a call writes the copy at the end of its workspace."""
+    db.workspace.fill_(255)
+    db.attend()
+    torch.cuda.synchronize()
+    return not bool((db.workspace[-copy_bytes:] == 255).all())
+
+
 def case(D, tail, docs):
     # request 0: cached documents of odd lengths and a tail over all of them (one
     # segment); request 1: detached query spans in one block with an unqueried span
@@ -55,6 +63,7 @@ def test_key_copy(D, style, tail, docs, table_len, rotary):
     say(f"[gpu] key copy D={D} style={style}: workspace {size}, partials {need}, {keys} keys in request 0")
     assert size >= need + keys * 8 * D * 2          # the copy is planned
     db.write()
+    assert was_copied(db, keys * 8 * D * 2)
     db.attend()
     torch.cuda.synchronize()
     ref = WO.run(wl, style="neox" if style == 0 else "gptj")
@@ -115,6 +124,7 @@ def test_key_copy_with_groups_in_the_workspace():
     before = shape["partial_slots"] * 256 * (128 + 2) * 4 + 67 * 48 + 4 * (shape["attention_blocks"] + shape["merge_blocks"])
     assert before + copy <= db.workspace.numel() <= before + copy + 4 * 256    # the copy comes last
     db.write()
+    assert was_copied(db, copy)
     ref = WO.run(wl)
     for got, what in zip(attend_both(db, wl, copy), ("copy", "no copy")):
         assert_close(got, ref, wl.dtype, f"{wl.name} {what}")
@@ -134,6 +144,7 @@ def test_key_copy_segments(n, copied):
     copy = sum((a + 207) // 16 - a // 16 + 1 for a in at) * 8 * 16 * 64 * 2
     assert (db.workspace.numel() >= copy) == copied
     db.write()
+    assert not copied or was_copied(db, copy)
     rows = list(range(0, 208 * n, 499))
     ref = WO.run(wl, rows=rows)
     for got, what in zip(attend_both(db, wl, copy if copied else 0), ("copy", "no copy")):
@@ -146,6 +157,7 @@ def test_key_copy_captured():
     wl = case(128, 208, (37, 1999, 705))
     db = DeviceBatch(wl, table_positions=int(wl.positions.max()) + 1)
     db.write()
+    assert was_copied(db, 4096)
     db.attend()
     torch.cuda.synchronize()
     ref = db.o.clone()
@@ -165,3 +177,20 @@ def test_key_copy_captured():
         torch.cuda.synchronize()
         say(f"  replay {r}: junk={float(junk):.3f}")
         assert torch.equal(db.o.view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("table,copied", [(True, False), (False, True)])
+def test_key_copy_of_many_short_items(table, copied):
+    # 190 one-token documents beside the tail: 1,900 items, which the alternating kernel would
+    # slow down by more than the copy saves, unless every item computed its cos/sin
+    from paper_2606_13126_amd.runner import DeviceBatch
+    spans = [Sp(n, S) for n in (37, 1999, 705)] + [Sp(1, S | Q, fresh=True) for _ in range(190)]
+    wl = W.small_case("key_copy_short_items", [spans + [Sp(208, Pd | Q, fresh=True)]], Hq=128, Hkv=8, D=128, theta=5e5,
+                      dtype=torch.bfloat16, seed=102, value_scale=0.5)
+    db = DeviceBatch(wl, table_positions=int(wl.positions.max()) + 1 if table else None)
+    copy = -(-int(wl.seq_lens[0]) // 16) * 8 * 16 * 128 * 2
+    assert db.workspace.numel() > copy
+    db.write()
+    assert was_copied(db, copy) == copied
+    rows = list(range(0, 190, 9)) + list(range(190, 398, 7))
+    assert_close(to_np(db.o)[rows], WO.run(wl, rows=rows), wl.dtype, f"{wl.name} table={table}")
