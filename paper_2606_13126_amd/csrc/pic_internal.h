@@ -77,12 +77,12 @@ struct Group {
     int32_t q_row0;      // row of tok0 in q / o
     int32_t win;         // window start of the span's tokens
     int32_t pos_off;     // offset of the request's token 0 in `positions`
+    int32_t krot0;       // block of the call's rotated key copy that holds sequence block 0 (may be negative)
     int32_t n_split;     // key splits per (row tile, KV head)
     int32_t split_keys;  // keys per split (a multiple of kTileKeys)
     int32_t item_base;   // first item (block index) of the group; a multiple of 8 (prefill)
     int32_t part_base;   // first partial slot (split groups)
     int32_t merge_base;  // first block of the merge launch (split groups)
-    int32_t krot0;       // block of the call's rotated key copy that holds sequence block 0 (may be negative)
 };
 
 // Row tiles of a group whose workgroups hold tile_rows query rows (kTileRows; float32:
@@ -166,7 +166,6 @@ struct Args {
     void* o;
     const void* k_pool;
     const void* v_pool;
-    const void* k_rot;        // the call's rotated copy of the keys its queries see, in the pool's layout, or null
     const int32_t* block_tables;
     const int32_t* positions;
     const float* rope_table;  // [rope_len][D/2] 8-byte entries (format by dtype) or null
@@ -181,6 +180,9 @@ struct Args {
     int32_t hq;
     int32_t hkv;
     int32_t group;            // G = hq / hkv
+    // the call's rotated copy of the keys its queries see, in the pool's layout, or null
+    // (last, so that the kernels without it load the pointers above in pairs as they lie)
+    const void* k_rot;
 };
 
 // Records msg as the thread's last error (pic_last_error) and returns st.
