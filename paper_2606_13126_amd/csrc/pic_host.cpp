@@ -377,14 +377,19 @@ WsLayout ws_layout(const pic_config* c, const HostPlan& hp) {
 // rotating in the attention kernel against copy + attention: one 33,280-token prompt
 // (20 row tiles per key) 903 against 784 us; 16 tails of 128 tokens over 4,096 keys (2
 // per key) 161 against 167 us; a 256-query tail over 5,376 keys (4 per key) 41 against
-// 50 us (the 10 us hold one item per CU).  prefill_direct adds about 1.1 us to every further
-// item of a CU (filling and draining its phases): 4,440 items that see 177 keys on average took 286 us
-// rotating in the kernel, 314 us with the copy; 2,240 that see 880, 388 against 328.  This
-// holds at head_dim 128 with a cos/sin table.  At head_dim 64, where both costs halve, every
-// call past the line gains all the same (13 requests, 1,096 items: 116 against 90 us; 16 x 128
-// queries over 5,120 keys 135 against 129), and without a table rotation in the kernel costs
-// far more (1,568 items: 222 against 170 us): there the items are not counted, and as the
-// table is known only to the call, it decides on them (keys_from_table).
+// 50 us.
+// That line is met where the planning ends.  Past it, at head_dim 128 with a cos/sin table,
+// many short items can still lose, since prefill_direct adds to every item (filling and
+// draining its phases): 4,440 items that see 177 keys on average took 286 us rotating in the
+// kernel, 314 us with the copy; 2,240 that see 880, 388 against 328.  Fitted to 4,236 calls
+// drawn within 30 us of the line (prompts of up to 33K tokens, inputs that change from call to
+// call), the copy saves 0.037 ns per key, row tile and KV head and costs 0.07 ns per key and
+// KV head, 1.2 us per item of a CU and 3.3 us, with 8 us of scatter: of the calls past the
+// first line 239 lose more than 2% by copying, of those past both 67.  Which side of the second
+// line a call is on is decided in the call (keys_from_table), since the workspace is planned
+// without the table.  At head_dim 64 every measured call past the first line gains (13
+// requests, 1,096 items: 116 against 90 us; 16 x 128 queries over 5,120 keys 135 against
+// 129), and without a table by far more (1,568 items: 222 against 170 us).
 // Calls of more than kMaxGroups segments or kMaxKeyCopy bytes rotate in the attention
 // kernel: where a copy of them would pay has not been measured (512 queries of 64 / 8 heads
 // over 131,072 keys, the most: 2,271 against 1,853 us).
@@ -418,7 +423,8 @@ void plan_keys(const pic_config* c, HostPlan& hp) {
     }
     const double gain_us = c->num_kv_heads * (0.043e-3 * staged - 0.07e-3 * (double)keys) - 10.0;
     if (gain_us <= 0 || segs.size() > (size_t)pic::kMaxGroups || key_copy_bytes(c, blocks) > pic::kMaxKeyCopy) return;
-    hp.keys_from_table = c->head_dim != 128 || gain_us > 1.1 * (items / pic::kTargetCUs - 1.0);
+    hp.keys_from_table = c->head_dim != 128 || c->num_kv_heads * (0.037e-3 * staged - 0.07e-3 * (double)keys) >
+                                                   1.2 * items / pic::kTargetCUs + 3.3;
     hp.keys.n = (int32_t)segs.size();
     int32_t blk = 0;
     for (size_t i = 0; i < segs.size(); ++i) {
