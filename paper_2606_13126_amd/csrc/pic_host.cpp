@@ -561,6 +561,8 @@ pic_status run_attention(const pic_config* c, const pic_batch_host* b, const pic
     a.part_o = hp.n_parts ? reinterpret_cast<float*>(wsb) : nullptr;
     const bool copy_keys = hp.keys.n > 0 && ws != nullptr && ws_bytes >= wl.total && (hp.keys_from_table || !table);
     a.k_rot = copy_keys ? wsb + wl.keys : nullptr;
+    if (!copy_keys && !hp.dec_kernel)
+        for (auto& g : hp.groups) g.n_rt = pic::row_tiles(g, c->num_q_heads / c->num_kv_heads, hp.tile_rows());
     a.part_ml = hp.n_parts ? reinterpret_cast<float*>(wsb + wl.ml) : nullptr;
     const double scale = c->softmax_scale > 0.f ? (double)c->softmax_scale : 1.0 / std::sqrt((double)c->head_dim);
     a.scale_log2 = (float)(scale * 1.4426950408889634);

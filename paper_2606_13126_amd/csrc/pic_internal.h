@@ -77,7 +77,10 @@ struct Group {
     int32_t q_row0;      // row of tok0 in q / o
     int32_t win;         // window start of the span's tokens
     int32_t pos_off;     // offset of the request's token 0 in `positions`
-    int32_t krot0;       // block of the call's rotated key copy that holds sequence block 0 (may be negative)
+    union {
+        int32_t n_rt;    // row tiles (calls without a rotated key copy)
+        int32_t krot0;   // block of the call's rotated key copy that holds sequence block 0 (may be negative)
+    };
     int32_t n_split;     // key splits per (row tile, KV head)
     int32_t split_keys;  // keys per split (a multiple of kTileKeys)
     int32_t item_base;   // first item (block index) of the group; a multiple of 8 (prefill)
@@ -86,8 +89,8 @@ struct Group {
 };
 
 // Row tiles of a group whose workgroups hold tile_rows query rows (kTileRows; float32:
-// 16 per wave).  Not a field: a dispatch whose arguments pass about 3.8 KB takes 2 us
-// longer on the host (44.6 against 47.0 us for a one-request decode step).
+// 16 per wave).  Not a field of its own: a dispatch whose arguments pass about 3.8 KB takes
+// 2 us longer on the host (44.6 against 47.0 us for a one-request decode step).
 __host__ __device__ inline int32_t row_tiles(const Group& g, int32_t group, int32_t tile_rows) {
     return (int32_t)(((int64_t)g.n_tok * group + tile_rows - 1) / tile_rows);
 }

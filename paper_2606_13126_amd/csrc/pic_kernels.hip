@@ -698,11 +698,12 @@ __global__ void __launch_bounds__(kThreads, 512 / kThreads) prefill_bf16(const P
     const Group g = group_of<false>(plan, bid);
     const int part_base = g.part_base;
     const int G = a.group;
-    const int rows_total = g.n_tok * G;
-    const int li = bid - g.item_base, n_rt = (rows_total + kTileRows - 1) / kTileRows;
+    // (computing the row tiles here, as the other kernels do, cost head_dim 64 about 1%)
+    const int li = bid - g.item_base, n_rt = g.n_rt;
     if (li >= a.hkv * g.n_split * n_rt) return;
     const ItemCoords ic = item_coords(g, a.hkv, n_rt, li);
     const int cluster = ic.cluster, rt = ic.rt, kvh = ic.kvh, split = ic.split;
+    const int rows_total = g.n_tok * G;
     const int row_lo = rt * kTileRows;
     const int row_hi = min(row_lo + kTileRows, rows_total);
     const int t_last = g.tok0 + (row_hi - 1) / G;
