@@ -9,9 +9,9 @@ fresh 512-token PDEP query tail: 33,280 tokens, 64/8 heads, head_dim 128, theta 
 bf16): pic_kv_write of the 16,896 fresh K/V rows followed by pic_attn_prefill.
 Inputs are resident in HBM before the timed region.  ``value`` is the algorithmic
 prefill work (4*D*Hq per visible query/key pair, 691.8 GFLOP) per step time, in
-TFLOP/s.  Extra fields time every other workload, the fused-RoPE overhead against
-the same kernel on pre-rotated K, the decode bandwidth, and the fp64 CPU oracle on
-this host.
+TFLOP/s.  Extra fields time every other workload, the overhead of the call that rotates
+(in the attention kernel, or once per call into a copy) against the same call on
+pre-rotated K, the decode bandwidth, and the fp64 CPU oracle on this host.
 """
 from __future__ import annotations
 
@@ -233,7 +233,8 @@ def bench_workload(wl, steps, warmup, stream, with_control=True):
     nt.k_pool, nt.v_pool = db.k_pool, db.v_pool
     out["attn_ms_computed_cossin"] = float(np.median(timed(nt.attend, steps, warmup, stream)))
     if with_control:
-        # same kernel, no RoPE (the pool is read as if it held rotated keys); ABAB timing
+        # the same call without RoPE (the pool is read as if it held rotated keys; for a
+        # prefill by another kernel than one that rotates); ABAB timing
         ctl = DeviceBatch(wl, k_prerotated=True, table_positions=None)
         ctl.k_pool, ctl.v_pool = db.k_pool, db.v_pool
         a_ms, b_ms = [], []

@@ -250,7 +250,8 @@ pic_status pic_plan_debug(const pic_config* cfg, const pic_batch_host* batch, in
  *  groups (query spans, or requests for decode), plan-upload launches that write the
  *  group table into the workspace (0 when the groups travel as kernel arguments),
  *  split partial slots}.  Every call is one attention launch and at most one merge
- *  launch, whatever the batch size.  No HIP call is made. */
+ *  launch, whatever the batch size (and one launch before them that rotates the keys,
+ *  where the workspace holds a copy of them).  No HIP call is made. */
 pic_status pic_plan_shape(const pic_config* cfg, const pic_batch_host* batch, int32_t is_decode, int32_t* shape);
 
 #ifdef __cplusplus
