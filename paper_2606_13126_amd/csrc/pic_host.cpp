@@ -205,11 +205,12 @@ pic_status make_plan(const pic_config* c, const pic_batch_host* b, bool decode, 
         // Decode items are (request, key split, group of KV heads).  A wide workgroup
         // holds a CU (narrow ones share it three or two ways), so cut the keys into
         // chunks of about the average work per resident workgroup (at least 4 cache
-        // blocks) and balance the splits of each request.  Finer chunks are faster (decode +
-        // merge, 4 against 2 blocks: one request of 1,537 keys 15.3 against 14.2 us, of 500
-        // keys 15.0 against 12.0) but less exact: a split rounds its probabilities to bf16
-        // relative to its own running maximum, and one request of 1,537 keys is 3.84e-3 from
-        // 64 bits in chunks of 2 blocks, 3.72e-3 in chunks of 4.
+        // blocks) and balance the splits of each request.  A split rounds its probabilities to
+        // bf16 relative to its own running maximum, so the chunks decide results beyond 32-bit
+        // rounding: chunks of 2 blocks are faster for few requests (decode + merge, 4 against
+        // 2 blocks: one request of 1,537 keys 15.3 against 14.2 us, of 500 keys 15.0 against
+        // 12.0) and as exact (3.73e-3 against 3.66e-3 from 64 bits, 16 inputs of 1,537 keys),
+        // but move their results by 2.5e-3.  4 keeps the results of a call what they have been.
         const int64_t n_hg = dec_head_groups(c);
         int64_t tiles_total = 0;
         for (auto& g : hp.groups)

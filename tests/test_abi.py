@@ -276,8 +276,8 @@ def test_plan_exact_cover_explicit_windows(dtype):
 @pytest.mark.parametrize("Hq,Hkv,D", [(32, 8, 128), (8, 2, 64), (4, 1, 128), (12, 12, 64)])
 @pytest.mark.parametrize("keys", [33, 64, 65, 500, 1537, 2048])
 def test_decode_chunks_hold_four_cache_blocks(Hq, Hkv, D, keys):
-    # finer chunks round more probabilities relative to the maximum of a few keys: their
-    # outputs are further from 64 bits
+    # a split rounds its probabilities to bf16 relative to its own maximum, so finer chunks
+    # would change the results of few-request decodes beyond 32-bit rounding
     hb = B.HostBatch([keys], [0, 1], [0], [W.PDEP])
     items = P.pic_plan_debug(P.make_config(Hq, Hkv, D), hb, True)
     splits = {(int(it[4]), int(it[5])) for it in items}
